@@ -641,9 +641,8 @@ def update_traffic_floor(wl, dev, reps=5, launches=4):
 
 def fp32_mfma_share(nb, nr, fused=True):
     """Executed MFMA flops of the float32 products over the algorithmic 8 flops per complex
-    multiply-add: the persistent fused kernel (at most 16 batch rows, at most 224
-    receivers) issues four real 16x16x4 products per complex one, the tiled and
-    warp-specialised kernels three."""
+    multiply-add: the fused product over at most 16 batch rows and 224 receivers issues four
+    real 16x16x4 products per complex one, the others three."""
     return 1.0 if fused and nb <= 16 and nr <= 224 else 0.75
 
 

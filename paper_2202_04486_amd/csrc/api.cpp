@@ -84,12 +84,6 @@ mdd_status check_dims(const mdd_dims* d) {
   return MDD_OK;
 }
 
-// Column groups of one frequency in the product kernels (must match launch_gemm).
-int gemm_ncg(int nb, int nvb) {
-  const int tnb = nb <= 16 ? 1 : (nb <= 32 ? 2 : 4);
-  return (nvb + tnb - 1) / tnb;
-}
-
 }  // namespace
 
 struct mdd_plan {
@@ -158,7 +152,9 @@ struct mdd_plan {
   // Float64 partials of ||g||^2 written by the gradient / update kernels.
   int n_gn() const { return (vs1() ? nblocks(d.nr) : d.nr * nvb) * trace_update_split(d.nt); }
   // Float64 loss partials written by one fused product launch over a batch of nb.
-  int n_loss(int nb) const { return d.nf * (vs1() ? gemv_groups(nb, d.nf) : gemm_ncg(nb, nvb)); }
+  int n_loss(int nb) const {
+    return d.nf * (vs1() ? gemv_groups(nb, d.nf) : gemm_loss_parts(d.precision, nb, nvb));
+  }
 
   template <class Fn>
   mdd_status run(int kclass, Fn&& fn) {

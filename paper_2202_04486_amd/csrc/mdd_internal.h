@@ -100,6 +100,11 @@ hipError_t launch_trace(int mode, const TraceArgs& a, hipStream_t s);
 // writes one float64 partial, so those launches write rows * ncb * split partials.
 int trace_update_split(int nt);
 hipError_t launch_gemm(int kind, int precision, const GemmArgs& a, hipStream_t s);
+// Float64 loss partials per frequency that the fused kind of launch_gemm writes.
+int gemm_loss_parts(int precision, int nb, int nvb);
+// Float32 products (gemm_rows.hip): every kind and batch size; the fused kind writes nf *
+// nvb loss partials.
+hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStream_t s);
 // bf16x3 / fp16x3 products (gemm_split.hip): 16 < nb <= NB_LIMIT, or the fused kind
 // at nb <= 16 over at most SPLIT_PIPE_KC receivers (persistent kernel).
 constexpr int SPLIT_PIPE_KC = 256;

@@ -1,0 +1,56 @@
+"""The float32 products at the edges of their tiles: batch rows around multiples of 16,
+receivers around the 32-receiver chunks and around the number of chunks that stay in LDS,
+columns around the 16-column blocks and the four blocks of a workgroup."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import freq
+
+from gpu_helpers import H, T, f32, make_plan, random_case, relerr
+
+pytestmark = pytest.mark.gpu
+
+# The spectra carry float32 rounding of about log2(nt) operations (1e-6 of their norm at
+# most) and the compensated products add less than that.
+TOL = 2e-6
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp32_cgemm"])
+@pytest.mark.parametrize("nb,nr,nvs", [(1, 1, 2), (1, 33, 17), (15, 31, 16), (16, 32, 65), (16, 320, 16),
+                                       (16, 321, 33), (17, 95, 64), (17, 97, 65), (32, 64, 130),
+                                       (33, 63, 18), (48, 65, 66), (49, 129, 20), (64, 40, 81)])
+def test_every_kind_at_tile_edges(prec, nb, nr, nvs):
+    ns, nt, nf = 70, 128, 41
+    d, u, r = random_case(ns, nr, nvs, nt, seed=nb + nr + nvs)
+    rng = np.random.default_rng(nb)
+    idx = rng.integers(0, ns, size=nb).astype(np.int32)
+    if nb > 4:
+        idx[1], idx[nb - 1] = -1, ns           # rejected entries act as zero sources
+        idx[3] = idx[2]
+    plan = make_plan(d, u, nb_max=nb, nf=nf, precision=prec)
+    good = (idx >= 0) & (idx < ns)
+    keep, ti = idx[good], T(idx, torch.int32)
+    out = torch.full((nb, nvs, nt), np.nan, device="cuda")
+    ug = H(plan.mdc_forward(T(r), ti, out=out))
+    assert relerr(ug[good], freq.mdc(d[keep], r, nf)) <= TOL
+    assert not ug[~good].any()
+    v = f32(rng.standard_normal((nb, nvs, nt)))
+    ga = H(plan.mdc_adjoint(T(v), ti))
+    assert relerr(ga, freq.mdc_adjoint(d[keep], v[good], nf)) <= TOL
+    G, loss, gn = plan.mdd_stoch_grad(T(r), ti)
+    lo, go = freq.batch_loss_grad(d, r, u, keep, nf)
+    assert relerr(H(G), go) <= TOL
+    assert abs(loss.item() - lo) <= TOL * lo
+    assert abs(gn.item() - np.sum(go ** 2)) <= 2 * TOL * np.sum(go ** 2)
+
+
+@pytest.mark.parametrize("nb", [3, 20, 40, 60])
+def test_batch_of_rejected_entries_is_zero(nb):
+    """No accepted entry: zero gradient and loss, also with kernel rows that are not finite."""
+    d, u, r = random_case(70, 50, 35, 128, seed=nb)
+    d[0] = np.inf
+    plan = make_plan(d, u, nb_max=nb, nf=30)
+    idx = T(np.full(nb, -1, dtype=np.int32), torch.int32)
+    G, loss, gn = plan.mdd_stoch_grad(T(r), idx)
+    assert not H(G).any() and loss.item() == 0.0 and gn.item() == 0.0
