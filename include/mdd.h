@@ -260,8 +260,9 @@ mdd_status mdd_step(mdd_plan* plan, float* R, float* s0, float* s1, const mdd_op
  * less the per-batch model transforms):
  *   loss = 1/2 sum_{s < ns} || p-_s - P+_s R ||^2                  (float64)
  *   G    = C_c [ - sum_{s < ns} P+_s^H (p-_s - P+_s R) ],  gnorm2 = || G ||^2
- * The sources are taken in order in batches of nb_max; R is transformed once and
- * the batches' adjoint products accumulate in the second spectra buffer.
+ * The sources are taken in order in batches of up to 64 (whatever nb_max); R is
+ * transformed once and the batches' adjoint products accumulate in the second spectra
+ * buffer.
  * G_out [nr][nvs][nt] float32; loss_out / gnorm2_out device float64 (may be NULL).
  * Needs kernel, data and MDD_FLAG_FULL_GRAD (MDD_ESTATE otherwise). */
 mdd_status mdd_full_grad(mdd_plan* plan, const float* R, float* G_out, double* loss_out,

@@ -11,6 +11,12 @@
 
 using namespace mdd;
 
+#define MDD_TRY(x)                 \
+  do {                             \
+    const mdd_status s_ = (x);     \
+    if (s_ != MDD_OK) return s_;   \
+  } while (0)
+
 namespace {
 
 constexpr int MAX_EXTENT = 4096;  // ns, nr, nvs: the power iteration keeps vectors in LDS
@@ -23,8 +29,18 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 bool valid_nt(int nt) { return nt == 128 || nt == 256 || nt == 512 || nt == 1024; }
 
 struct Layout {
-  size_t tw, df, uf, oob, oobp, onset, f, bsp, lossp, gnp, dmx, red2, f2, sidx, lossb, gvp, total;
+  size_t tw, df, uf, oob, oobp, onset, f, bsp, lossp, gnp, dmx, red2, f2, sidx, gvp, total;
 };
+
+// Sources per batch of the full gradient, whatever nb_max: the largest batch the products
+// take, since each batch reads R_k and reads and writes G_k once more (the 2D line: 13
+// batches of 16 825 us an iteration, 3 of 64 and one of 9 549 us).
+int full_batch(const mdd_dims& d) { return d.ns < NB_LIMIT ? d.ns : NB_LIMIT; }
+
+size_t max_gemv_groups(int nb_a, int nb_b, int nf) {
+  const int a = gemv_groups(nb_a, nf), b = nb_b > 0 ? gemv_groups(nb_b, nf) : 0;
+  return a > b ? a : b;
+}
 
 Layout make_layout(const mdd_dims& d) {
   const size_t nrp = round16(d.nr), nvsp = round16(d.nvs), nvb = nblocks(d.nvs);
@@ -49,17 +65,18 @@ Layout make_layout(const mdd_dims& d) {
   L.onset = take(sizeof(int32_t) * d.nr * d.nvs);
   L.f = take(c8 * d.nr * nvb * d.nf * CB);
   L.bsp = take(c8 * d.nb_max * nvb * d.nf * CB);
-  // nvs = 1: the matrix-vector products write one loss partial per row group.
-  const size_t ngv = d.nvs == 1 ? gemv_groups(d.nb_max, d.nf) : 0;
-  L.lossp = take(sizeof(double) * d.nf * (ngv > nvb ? ngv : nvb));
+  // nvs = 1: the matrix-vector products write one loss partial per row group.  The full
+  // gradient takes the sources in batches of full_batch and keeps every batch's partials.
+  const bool full = (d.flags & MDD_FLAG_FULL_GRAD) != 0;
+  const size_t fb = full_batch(d), nsub = full ? (d.ns + fb - 1) / fb : 1;
+  const size_t ngv = d.nvs == 1 ? max_gemv_groups(d.nb_max, full ? fb : 0, d.nf) : 0;
+  L.lossp = take(sizeof(double) * d.nf * (ngv > nvb ? ngv : nvb) * nsub);
   // gradient / update modes: one partial per workgroup, trace_update_split(nt) per block
   L.gnp = take(sizeof(double) * d.nr * nvb * trace_update_split(d.nt));
   L.dmx = take(sizeof(float) * d.nf);               // per-frequency max |D| (fp16 scaling)
   L.red2 = take(sizeof(double) * 512);              // two-level reduction stage
-  const bool full = (d.flags & MDD_FLAG_FULL_GRAD) != 0;  // full gradient: G buffer, sources, losses
   L.f2 = take(full ? c8 * d.nr * nvb * d.nf * CB : 0);
   L.sidx = take(full ? sizeof(int32_t) * d.ns : 0);
-  L.lossb = take(full ? sizeof(double) * ((d.ns + d.nb_max - 1) / d.nb_max) : 0);
   L.gvp = take(ngv > 1 ? sizeof(float4) * d.nf * ngv * (nrp / 2) : 0);  // row-group partials
   L.total = o;
   return L;
@@ -122,7 +139,6 @@ struct mdd_plan {
   float* dmx() const { return at<float>(L.dmx); }
   double* red2() const { return at<double>(L.red2); }
   int32_t* sidx() const { return at<int32_t>(L.sidx); }
-  double* lossb() const { return at<double>(L.lossb); }
   float4* gvp() const { return at<float4>(L.gvp); }
   bool full() const { return (d.flags & MDD_FLAG_FULL_GRAD) != 0; }
   // MDD_FLAG_STREAM_KERNEL: Df holds the rows of the last staged batch (staged_nb rows).
@@ -258,32 +274,34 @@ struct mdd_plan {
     return run(MDD_KC_REDUCE, [&] { return launch_reduce(r, stream); });
   }
 
-  // Full gradient, products part: every source in order, batches of nb_max, the
-  // adjoint products summed into F2; batch j's loss into lossb[j].  F keeps R_k.
-  mdd_status full_products() {
-    const int nsub = (d.ns + d.nb_max - 1) / d.nb_max;
-    for (int j = 0; j < nsub; ++j) {
-      const int nb = d.ns - j * d.nb_max < d.nb_max ? d.ns - j * d.nb_max : d.nb_max;
-      const int32_t* idx = sidx() + (size_t)j * d.nb_max;
-      GemmArgs g = gemm(idx, nb);
+  // Full gradient, products part: every source in order in batches of full_batch, the
+  // adjoint products summed into F2, the batches' loss partials one after another.  F
+  // keeps R_k.
+  mdd_status full_products(int* n_partials) {
+    const int step = full_batch(d);
+    int at = 0;
+    for (int s0 = 0; s0 < d.ns; s0 += step) {
+      const int nb = d.ns - s0 < step ? d.ns - s0 : step;
+      GemmArgs g = gemm(sidx() + s0, nb);
       g.Gout = F2();
-      g.gacc = j > 0 ? 1 : 0;
-      mdd_status st = products(GK_FUSED, g);
-      if (st != MDD_OK) return st;
-      st = reduce(idx, nb, true, lossb() + j, nullptr);
-      if (st != MDD_OK) return st;
+      g.gacc = s0 > 0 ? 1 : 0;
+      g.loss_part += at;
+      at += n_loss(nb);
+      MDD_TRY(products(GK_FUSED, g));
     }
+    *n_partials = at;
     return MDD_OK;
   }
 
-  // Full gradient, final sums: the batches' losses in order and ||g||^2.
-  mdd_status full_reduce(double* loss_out, double* gnorm2_out) {
+  // Full gradient, final sums: the batches' loss partials, every source's out-of-band
+  // energy and ||g||^2.
+  mdd_status full_reduce(int n_partials, double* loss_out, double* gnorm2_out) {
     if (!loss_out && !gnorm2_out) return MDD_OK;
     ReduceArgs r{};
-    r.loss_part = lossb();
-    r.n_loss = (d.ns + d.nb_max - 1) / d.nb_max;
-    r.loss_scale = 1.0;
-    r.oob = nullptr;
+    r.loss_part = lossp();
+    r.n_loss = loss_out ? n_partials : 0;
+    r.loss_scale = 1.0 / (2.0 * d.nt);
+    r.oob = oob();
     r.idx = nullptr;
     r.nb = 0;
     r.ns = d.ns;
@@ -329,12 +347,6 @@ mdd_status update_args(const mdd_opt& o, float* s0, float* s1, TraceArgs& a, int
   }
   return MDD_OK;
 }
-
-#define MDD_TRY(x)                 \
-  do {                             \
-    const mdd_status s_ = (x);     \
-    if (s_ != MDD_OK) return s_;   \
-  } while (0)
 
 extern "C" {
 
@@ -652,7 +664,8 @@ mdd_status mdd_full_grad(mdd_plan* p, const float* R, float* G_out, double* loss
   if (!p->kernel_set || !p->data_set || !p->full()) return MDD_ESTATE;
   p->spec_model = nullptr;
   MDD_TRY(p->model_fft(R, nullptr, 0.0));
-  MDD_TRY(p->full_products());
+  int n_partials = 0;
+  MDD_TRY(p->full_products(&n_partials));
   TraceArgs a = p->blocked(p->F2(), p->d.nr);
   a.x_out = G_out;
   a.onset = p->mask_set ? p->onset() : nullptr;
@@ -663,7 +676,7 @@ mdd_status mdd_full_grad(mdd_plan* p, const float* R, float* G_out, double* loss
     p->spec_vel = nullptr;
     p->spec_mu = 0.0;
   }
-  return p->full_reduce(loss_out, gnorm2_out);
+  return p->full_reduce(n_partials, loss_out, gnorm2_out);
 }
 
 mdd_status mdd_full_step(mdd_plan* p, float* R, float* s0, float* s1, const mdd_opt* opt,
@@ -679,7 +692,8 @@ mdd_status mdd_full_step(mdd_plan* p, float* R, float* s0, float* s1, const mdd_
   const bool have = store && p->spec_model == R && p->spec_vel == vel && p->spec_mu == mu;
   p->spec_model = nullptr;
   if (!have) MDD_TRY(p->model_fft(R, vel, mu));
-  MDD_TRY(p->full_products());
+  int n_partials = 0;
+  MDD_TRY(p->full_products(&n_partials));
   a.model = R;
   a.store_spec = store ? 1 : 0;
   a.onset = p->mask_set ? p->onset() : nullptr;
@@ -691,7 +705,7 @@ mdd_status mdd_full_step(mdd_plan* p, float* R, float* s0, float* s1, const mdd_
     p->spec_vel = vel;
     p->spec_mu = mu;
   }
-  return p->full_reduce(loss_out, gnorm2_out);
+  return p->full_reduce(n_partials, loss_out, gnorm2_out);
 }
 
 mdd_status mdd_reciprocity(const float* z, float* out, int32_t n, int32_t nt, void* stream) {

@@ -31,7 +31,7 @@ struct ReduceArgs {
   int n_loss;
   double loss_scale;      // 1 / (2 nt)
   const double* oob;      // [ns] per-source out-of-band energy (already / (2 nt))
-  const int32_t* idx;
+  const int32_t* idx;     // NULL: the out-of-band energies of all ns sources
   int nb, ns;
   int oob_pos;            // 1: oob[b] for batch entry b (staged data), else oob[idx[b]]
   const double* gn_part;

@@ -11,8 +11,8 @@ namespace {
 
 constexpr int RED_THREADS = 1024;
 
-// loss = scale * sum(loss partials) + sum_b oob[idx[b]] (oob[b] for staged data);
-// gnorm2 = sum(gnorm partials).
+// loss = scale * sum(loss partials) + sum_b oob[idx[b]] (oob[b] for staged data, every
+// source's for the full gradient, idx NULL); gnorm2 = sum(gnorm partials).
 // The per-source constants are gathered by one thread each (no serial chain of
 // dependent loads) and added in batch order.
 __global__ __launch_bounds__(RED_THREADS) void k_reduce(ReduceArgs a) {
@@ -28,8 +28,9 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce(ReduceArgs a) {
   }
   const double l = block_fixed_sum<RED_THREADS>(a.loss_part, a.n_loss, red);
   const double g = block_fixed_sum<RED_THREADS>(a.gn_part, a.n_gn, red);
+  const double all = a.oob && !a.idx ? block_fixed_sum<RED_THREADS>(a.oob, a.ns, red) : 0.0;
   if (threadIdx.x == 0) {
-    double o = 0.0;
+    double o = all;
     for (int b = 0; b < a.nb; ++b) o += s_oob[b];
     if (a.loss_out) a.loss_out[0] = l * a.loss_scale + o;
     if (a.gnorm2_out) a.gnorm2_out[0] = g;

@@ -54,3 +54,20 @@ def test_batch_of_rejected_entries_is_zero(nb):
     idx = T(np.full(nb, -1, dtype=np.int32), torch.int32)
     G, loss, gn = plan.mdd_stoch_grad(T(r), idx)
     assert not H(G).any() and loss.item() == 0.0 and gn.item() == 0.0
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", TOL), ("bf16x3", 1e-3)])
+@pytest.mark.parametrize("ns,nvs", [(64, 20), (130, 35), (130, 1), (193, 16)])
+def test_full_gradient_in_batches_of_64(prec, tol, ns, nvs):
+    """More sources than one batch of 64, whatever nb_max: whole and ragged last batches."""
+    from paper_2202_04486_amd.plan import Plan
+    nr, nt, nf = 33, 128, 40
+    d, u, r = random_case(ns, nr, nvs, nt, seed=ns + nvs)
+    plan = Plan(ns, nr, nvs, nt, nf, 3, precision=prec, full_grad=True)
+    plan.mdd_set_kernel(T(d))
+    plan.mdd_set_data(T(u))
+    G, loss, gn = plan.mdd_full_grad(T(r))
+    lo, go = freq.batch_loss_grad(d, r, u, np.arange(ns), nf)
+    assert relerr(H(G), go) <= tol
+    assert abs(loss.item() - lo) <= tol * lo
+    assert abs(gn.item() - np.sum(go ** 2)) <= 2 * tol * np.sum(go ** 2)
