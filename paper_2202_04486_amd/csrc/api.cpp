@@ -19,7 +19,7 @@ using namespace mdd;
 
 namespace {
 
-constexpr int MAX_EXTENT = 4096;  // ns, nr, nvs: the power iteration keeps vectors in LDS
+constexpr int MAX_EXTENT = 4096;  // ns, nr, nvs: the power iteration keeps rows in registers
 // ns of a plan with MDD_FLAG_STREAM_KERNEL: such a plan runs no power iteration and
 // keeps no per-source kernel spectra (and, with MDD_FLAG_STREAM_DATA, no per-source data).
 constexpr int MAX_STREAM_NS = 1 << 20;
@@ -768,8 +768,10 @@ mdd_status mdd_sigma_max2(mdd_plan* p, int32_t iters, double* lam_out) {
   if (!p || !lam_out) return MDD_EINVAL;
   if (iters < 1) return MDD_EINVAL;
   if (!p->kernel_set || p->streamed()) return MDD_ESTATE;  // needs every source's D_k
+  p->spec_model = nullptr;  // the model spectra's buffer holds the iteration's partial sums
   return p->run(MDD_KC_REDUCE, [&] {
-    return launch_sigma(p->Df(), p->d.nf, p->d.ns, p->d.nr, p->nrp, iters, lam_out, p->stream);
+    return launch_sigma(p->Df(), p->d.nf, p->d.ns, p->d.nr, p->nrp, iters,
+                        sigma_groups(p->d.nf, p->d.ns, p->d.nr, p->nvb), p->F(), lam_out, p->stream);
   });
 }
 

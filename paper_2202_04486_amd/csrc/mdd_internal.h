@@ -123,8 +123,12 @@ hipError_t launch_spec_reciprocity(float2* X, int n, int nf, long long s_row, lo
                                    hipStream_t s);
 hipError_t launch_freq_absmax(const float2* Df, int nf, long long count, long long stride,
                               float* out, hipStream_t s);
-hipError_t launch_sigma(const float2* Df, int nf, int ns, int nr, int nrp, int iters,
-                        double* lam_out, hipStream_t s);
+// Power iterations: one launch each, P row groups per frequency; `scratch` holds two sets
+// of group partials [nf][P][nr] complex float64 and [nf][P] float64.  sigma_groups keeps
+// that within 128 nr nvb nf bytes, the model spectra's size.
+int sigma_groups(int nf, int ns, int nr, int nvb);
+hipError_t launch_sigma(const float2* Df, int nf, int ns, int nr, int nrp, int iters, int P,
+                        void* scratch, double* lam_out, hipStream_t s);
 
 // Measurement aid (calibrate.hip): the update kernel's HBM traffic without its transforms.
 hipError_t launch_calibrate_update(float* R, float* M, float* V, float2* spec, int rows,

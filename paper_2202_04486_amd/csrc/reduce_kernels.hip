@@ -3,6 +3,8 @@
 // the small helpers: the reciprocity average (z + z^T) / 2, per-frequency maxima of
 // D_k, the list of every source.  Every sum runs in a fixed order (no atomics), so
 // results are bitwise reproducible run to run.
+#include <algorithm>
+
 #include "device_common.h"
 #include "mdd_internal.h"
 
@@ -61,80 +63,261 @@ __global__ void k_row_sum(const double* part, int rows, int cols, double scale, 
   }
 }
 
-// Power iteration on D_k^H D_k (all ns sources) for one frequency per
-// workgroup.  Returns the Rayleigh quotient ||D_k v||^2 of the final unit v.
-__global__ __launch_bounds__(256) void k_sigma(const float2* Df, int ns, int nr, int nrp, int iters,
-                                               double* lam_out) {
-  extern __shared__ double smem_d[];
-  double* vr = smem_d;            // [nr] real / imag of v (then of z)
-  double* vi = vr + nr;
-  double* yr = vi + nr;           // [ns]
-  double* yi = yr + ns;
-  __shared__ double red[4];
-  __shared__ double bc;
-  const int k = blockIdx.x;
-  const float2* D = Df + (size_t)k * ns * nrp;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Sum of one double per lane over the wavefront, in every lane: rotations within 16 lanes,
+// then the four rows' sums through scalar registers (no LDS traffic).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int2 x = __builtin_bit_cast(int2, v);
+  int2 y;
+  y.x = __builtin_amdgcn_update_dpp(0, x.x, CTRL, 0xf, 0xf, false);
+  y.y = __builtin_amdgcn_update_dpp(0, x.y, CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int2 x = __builtin_bit_cast(int2, v);
+  int2 y;
+  y.x = __builtin_amdgcn_readlane(x.x, lane);
+  y.y = __builtin_amdgcn_readlane(x.y, lane);
+  return __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ double row16_sum(double v) {  // in every lane of each 16
+  v += dpp_move<0x128>(v);  // row_ror 8, 4, 2, 1
+  v += dpp_move<0x124>(v);
+  v += dpp_move<0x122>(v);
+  v += dpp_move<0x121>(v);
+  return v;
+}
+__device__ __forceinline__ double wave_sum_all(double v) {
+  v = row16_sum(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+// a + b with halves (HALF 32) or odd and even 16-lane rows (HALF 16) exchanged between the
+// two: the lower half (the even rows) of the result sums a over the exchanged pairs of
+// lanes, the upper half (the odd rows) sums b.
+template <int HALF>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+  uint2 p, q;
+  if constexpr (HALF == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false);
+    p = make_uint2(lo[0], hi[0]);
+    q = make_uint2(lo[1], hi[1]);
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    p = make_uint2(lo[0], hi[0]);
+    q = make_uint2(lo[1], hi[1]);
+  }
+  return __builtin_bit_cast(double, p) + __builtin_bit_cast(double, q);
+}
+// Sums over the wavefront of two complex values at once: the four parts share the steps.
+__device__ __forceinline__ void wave_sum_pair(double2& a, double2& b) {
+  const double v = row16_sum(swap_add<16>(swap_add<32>(a.x, a.y), swap_add<32>(b.x, b.y)));
+  a = make_double2(lane_value(v, 0), lane_value(v, 32));
+  b = make_double2(lane_value(v, 16), lane_value(v, 48));
+}
 
+// One power iteration on D_k^H D_k (all ns sources), float64: the workgroup of row group p
+// of frequency k normalises v = sum of the previous iteration's group partials (or the
+// start vector), and for each of its rows s forms y_s = D_k[s, :] v and, the row still in
+// registers, adds conj(D_k[s, :]) y_s to its partial of z = D_k^H D_k v.  The last
+// iteration writes the group's part of the Rayleigh quotient ||D_k v||^2 instead.
+//
+// Bound by the bytes of D_k, which is read once per iteration, by P workgroups: 86 MB in
+// 20 us at 201 x 201 and 257 bins (4.3 TB/s, from the last-level cache), 188 MB in 38 us at
+// 301 x 301.  Before, one workgroup per frequency read D_k twice an iteration and reduced
+// row by row: 129 us at the first size.  Two rows share the steps of their sums
+// (wave_sum_pair), the row base is a scalar, and two groups of rows are in flight.
+//
+// SPLIT: the row is spread over the workgroup's wavefronts (more than 512 receivers) and
+// each pair of rows is reduced across them through LDS; otherwise every wavefront holds
+// whole rows, and the wavefronts' partials are added once at the end.
+template <int MQ, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 512 : 256) void k_sigma_pass(const float2* Df, int ns, int nr, int nrp,
+                                                                  int P, int first, int last, const double2* zin,
+                                                                  double2* zout, double* lamp) {
+  constexpr int RB = 2;                            // rows per group, two groups in flight
+  extern __shared__ double2 s_z[];                 // !SPLIT: [wavefronts][MQ * 128]
+  __shared__ double2 s_y[2][RB][8];
+  __shared__ double s_n[8];
+  const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = gridDim.x, bid = blockIdx.x, full = (total / 8) * 8;
+  const int logical = bid < full ? (bid % 8) * (total / 8) + bid / 8 : bid;  // one XCD per frequency
+  const int k = logical / P, p = logical % P;
+  const int npair = nrp / 2, q0 = (SPLIT ? wave * MQ * 64 : 0) + lane;
+  const char* D = reinterpret_cast<const char*>(Df) + (long long)k * ns * nrp * 8;
+
+  const int i0 = (int)((long long)ns * p / P), i1 = (int)((long long)ns * (p + 1) / P);
+  const int stride = SPLIT ? RB : RB * nw;
+  const int ifirst = i0 + (SPLIT ? 0 : RB * wave);
+  unsigned qoff[MQ];                               // byte offsets of the lane's pairs in a row
+#pragma unroll
+  for (int m = 0; m < MQ; ++m) qoff[m] = 16u * min(q0 + 64 * m, npair - 1);
+  float4 d0[RB][MQ], d1[RB][MQ];
+  auto load_rows = [&](float4 (&d)[RB][MQ], int i) {
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      const char* row = D + (long long)min(i + b, i1 - 1) * nrp * 8;
+#pragma unroll
+      for (int m = 0; m < MQ; ++m) d[b][m] = *reinterpret_cast<const float4*>(row + qoff[m]);
+    }
+  };
+  load_rows(d0, ifirst);                           // in flight while v is formed
+  load_rows(d1, ifirst + stride);
+
+  // v: receivers 2 q, 2 q + 1 for q = q0 + 64 m (zero past nr).  The group partials are
+  // requested GB at a time and added in group order.
+  double2 v[MQ][2], z[MQ][2];
+#pragma unroll
+  for (int m = 0; m < MQ; ++m)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = 2 * (q0 + 64 * m) + h;
+      v[m][h] = z[m][h] = make_double2(0.0, 0.0);
+      if (first && r < nr)                         // deterministic, non-degenerate start
+        v[m][h] = make_double2(1.0 + 0.25 * (double)((r * 37) % 11), 0.1 * (double)((r * 17) % 7));
+    }
+  if (!first) {
+    constexpr int GB = MQ <= 2 ? 4 : 2;
+    const double2* part = zin + (long long)k * P * nr;
+#pragma unroll 1
+    for (int g0 = 0; g0 < P; g0 += GB) {
+      double2 t[GB][MQ][2];
+#pragma unroll
+      for (int g = 0; g < GB; ++g)
+#pragma unroll
+        for (int m = 0; m < MQ; ++m)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            t[g][m][h] = part[(long long)min(g0 + g, P - 1) * nr + min(2 * (q0 + 64 * m) + h, nr - 1)];
+#pragma unroll
+      for (int g = 0; g < GB; ++g)
+#pragma unroll
+        for (int m = 0; m < MQ; ++m)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (g0 + g < P && 2 * (q0 + 64 * m) + h < nr) {
+              v[m][h].x += t[g][m][h].x;
+              v[m][h].y += t[g][m][h].y;
+            }
+    }
+  }
   double n2 = 0.0;
-  for (int r = tid; r < nr; r += 256) {  // deterministic, non-degenerate start
-    vr[r] = 1.0 + 0.25 * (double)((r * 37) % 11);
-    vi[r] = 0.1 * (double)((r * 17) % 7);
-    n2 += vr[r] * vr[r] + vi[r] * vi[r];
+#pragma unroll
+  for (int m = 0; m < MQ; ++m)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) n2 += v[m][h].x * v[m][h].x + v[m][h].y * v[m][h].y;
+  n2 = wave_sum_all(n2);
+  if constexpr (SPLIT) {
+    if (lane == 0) s_n[wave] = n2;
+    __syncthreads();
+    n2 = 0.0;
+    for (int w = 0; w < nw; ++w) n2 += s_n[w];
+    __syncthreads();
   }
-  n2 = block_sum256(n2, red);
-  if (tid == 0) bc = 1.0 / sqrt(n2);
-  __syncthreads();
-  for (int r = tid; r < nr; r += 256) {
-    vr[r] *= bc;
-    vi[r] *= bc;
-  }
-  __syncthreads();
+  const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+#pragma unroll
+  for (int m = 0; m < MQ; ++m)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      v[m][h].x *= inv;
+      v[m][h].y *= inv;
+    }
 
   double lam = 0.0;
-  for (int it = 0; it < iters; ++it) {
-    double ynorm = 0.0;
-    for (int s = wave; s < ns; s += 4) {  // y = D v
-      double ar = 0.0, ai = 0.0;
-      for (int r = lane; r < nr; r += 64) {
-        const float2 d = D[(size_t)s * nrp + r];
-        ar += (double)d.x * vr[r] - (double)d.y * vi[r];
-        ai += (double)d.x * vi[r] + (double)d.y * vr[r];
+  auto group = [&](int i, int par, float4 (&d)[RB][MQ]) {
+    double2 y[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      double re = 0.0, im = 0.0;
+#pragma unroll
+      for (int m = 0; m < MQ; ++m) {
+        const double a0 = d[b][m].x, b0 = d[b][m].y, a1 = d[b][m].z, b1 = d[b][m].w;
+        re += a0 * v[m][0].x - b0 * v[m][0].y;
+        im += a0 * v[m][0].y + b0 * v[m][0].x;
+        re += a1 * v[m][1].x - b1 * v[m][1].y;
+        im += a1 * v[m][1].y + b1 * v[m][1].x;
       }
-      ar = wave_sum(ar);
-      ai = wave_sum(ai);
-      if (lane == 0) {
-        yr[s] = ar;
-        yi[s] = ai;
-        ynorm += ar * ar + ai * ai;
+      y[b] = make_double2(re, im);
+    }
+    wave_sum_pair(y[0], y[1]);
+    if constexpr (SPLIT) {
+      if (lane == 0)
+        for (int b = 0; b < RB; ++b) s_y[par][b][wave] = y[b];
+      __syncthreads();  // the other buffer (par ^ 1) is free again after this barrier
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        y[b] = make_double2(0.0, 0.0);
+        for (int w = 0; w < nw; ++w) {
+          y[b].x += s_y[par][b][w].x;
+          y[b].y += s_y[par][b][w].y;
+        }
       }
     }
-    ynorm = block_sum256(ynorm, red);
-    if (tid == 0) bc = ynorm;
-    __syncthreads();
-    lam = bc;
-    double z2 = 0.0;
-    for (int r = tid; r < nr; r += 256) {  // z = D^H y, written over v
-      double zr = 0.0, zi = 0.0;
-      for (int s = 0; s < ns; ++s) {
-        const float2 d = D[(size_t)s * nrp + r];
-        zr += (double)d.x * yr[s] + (double)d.y * yi[s];
-        zi += (double)d.x * yi[s] - (double)d.y * yr[s];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      if constexpr (MQ > 2) {  // converted again: the float64 values would take the registers
+#pragma unroll                 // of the rows in flight
+        for (int m = 0; m < MQ; ++m)
+          asm volatile("" : "+v"(d[b][m].x), "+v"(d[b][m].y), "+v"(d[b][m].z), "+v"(d[b][m].w));
       }
-      vr[r] = zr;
-      vi[r] = zi;
-      z2 += zr * zr + zi * zi;
+      if (i + b >= i1) y[b] = make_double2(0.0, 0.0);
+      lam += y[b].x * y[b].x + y[b].y * y[b].y;
+#pragma unroll
+      for (int m = 0; m < MQ; ++m) {
+        const double a0 = d[b][m].x, b0 = d[b][m].y, a1 = d[b][m].z, b1 = d[b][m].w;
+        z[m][0].x += a0 * y[b].x + b0 * y[b].y;
+        z[m][0].y += a0 * y[b].y - b0 * y[b].x;
+        z[m][1].x += a1 * y[b].x + b1 * y[b].y;
+        z[m][1].y += a1 * y[b].y - b1 * y[b].x;
+      }
     }
-    z2 = block_sum256(z2, red);
-    if (tid == 0) bc = z2 > 0.0 ? 1.0 / sqrt(z2) : 0.0;
-    __syncthreads();
-    for (int r = tid; r < nr; r += 256) {
-      vr[r] *= bc;
-      vi[r] *= bc;
-    }
-    __syncthreads();
+    load_rows(d, i + 2 * stride);
+  };
+#pragma unroll 1
+  for (int i = ifirst; i < i1; i += 2 * stride) {
+    group(i, 0, d0);
+    if (i + stride >= i1) break;
+    group(i + stride, 1, d1);
   }
-  if (tid == 0) lam_out[k] = lam;
+
+  if (last) {
+    if constexpr (!SPLIT) {
+      if (lane == 0) s_n[wave] = lam;
+      __syncthreads();
+      lam = 0.0;
+      for (int w = 0; w < nw; ++w) lam += s_n[w];
+    }
+    if (tid == 0) lamp[(long long)k * P + p] = lam;
+    return;
+  }
+  double2* out = zout + ((long long)k * P + p) * nr;
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int m = 0; m < MQ; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = 2 * (q0 + 64 * m) + h;
+        if (r < nr) out[r] = z[m][h];
+      }
+  } else {
+#pragma unroll
+    for (int m = 0; m < MQ; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) s_z[wave * MQ * 128 + 2 * (lane + 64 * m) + h] = z[m][h];
+    __syncthreads();
+    for (int r = tid; r < nr; r += blockDim.x) {
+      double2 x = s_z[r];
+      for (int w = 1; w < nw; ++w) {
+        const double2 t = s_z[w * MQ * 128 + r];
+        x.x += t.x;
+        x.y += t.y;
+      }
+      out[r] = x;
+    }
+  }
 }
 
 // Largest |Re| or |Im| of D_k over all sources and receivers, per frequency (the
@@ -266,14 +449,35 @@ hipError_t launch_row_sum(const double* part, int rows, int cols, double scale, 
   return hipGetLastError();
 }
 
-hipError_t launch_sigma(const float2* Df, int nf, int ns, int nr, int nrp, int iters,
-                        double* lam_out, hipStream_t s) {
-  const size_t sm = sizeof(double) * 2 * ((size_t)nr + ns);
-  if (sm > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sigma),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-  hipLaunchKernelGGL(k_sigma, dim3(nf), dim3(256), sm, s, Df, ns, nr, nrp, iters, lam_out);
-  return hipGetLastError();
+int sigma_groups(int nf, int ns, int nr, int nvb) {
+  const int want = (3 * 256 + nf / 2) / nf;        // about three workgroups per CU,
+  const int most = (ns + 15) / 16;                 // at least 16 rows each,
+  const int room = std::min(4 * nvb - 1, 4 * nr);  // and 32 P nr + 8 P <= 128 nr nvb bytes
+  return std::max(1, std::min(want, std::min(most, room)));
+}
+
+hipError_t launch_sigma(const float2* Df, int nf, int ns, int nr, int nrp, int iters, int P,
+                        void* scratch, double* lam_out, hipStream_t s) {
+  double2* z[2] = {static_cast<double2*>(scratch), static_cast<double2*>(scratch) + (size_t)nf * P * nr};
+  double* lamp = reinterpret_cast<double*>(z[1] + (size_t)nf * P * nr);
+  const int npair = nrp / 2;
+  auto go = [&](auto kernel, int nw, size_t sm) {
+    for (int it = 0; it < iters; ++it) {
+      hipLaunchKernelGGL(kernel, dim3(nf * P), dim3(64 * nw), sm, s, Df, ns, nr, nrp, P, it == 0,
+                         it == iters - 1, z[(it + 1) & 1], z[it & 1], lamp);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
+  auto whole = [&](auto kernel, int mq) { return go(kernel, 4, sizeof(double2) * 4 * mq * 128); };
+  hipError_t e;
+  if (npair <= 64) e = whole(k_sigma_pass<1, false>, 1);
+  else if (npair <= 128) e = whole(k_sigma_pass<2, false>, 2);
+  else if (npair <= 192) e = whole(k_sigma_pass<3, false>, 3);
+  else if (npair <= 256) e = whole(k_sigma_pass<4, false>, 4);
+  else e = go(k_sigma_pass<4, true>, (npair + 255) / 256, 0);
+  return e == hipSuccess ? launch_row_sum(lamp, nf, P, 1.0, lam_out, s) : e;
 }
 
 }  // namespace mdd
