@@ -37,8 +37,8 @@ struct Layout {
 // batches of 16 825 us an iteration, 3 of 64 and one of 9 549 us).
 int full_batch(const mdd_dims& d) { return d.ns < NB_LIMIT ? d.ns : NB_LIMIT; }
 
-size_t max_gemv_groups(int nb_a, int nb_b, int nf) {
-  const int a = gemv_groups(nb_a, nf), b = nb_b > 0 ? gemv_groups(nb_b, nf) : 0;
+size_t max_gemv_groups(int nb_a, int nb_b, int nf, int nr) {
+  const int a = gemv_groups(nb_a, nf, nr), b = nb_b > 0 ? gemv_groups(nb_b, nf, nr) : 0;
   return a > b ? a : b;
 }
 
@@ -69,7 +69,7 @@ Layout make_layout(const mdd_dims& d) {
   // gradient takes the sources in batches of full_batch and keeps every batch's partials.
   const bool full = (d.flags & MDD_FLAG_FULL_GRAD) != 0;
   const size_t fb = full_batch(d), nsub = full ? (d.ns + fb - 1) / fb : 1;
-  const size_t ngv = d.nvs == 1 ? max_gemv_groups(d.nb_max, full ? fb : 0, d.nf) : 0;
+  const size_t ngv = d.nvs == 1 ? max_gemv_groups(d.nb_max, full ? fb : 0, d.nf, d.nr) : 0;
   L.lossp = take(sizeof(double) * d.nf * (ngv > nvb ? ngv : nvb) * nsub);
   // gradient / update modes: one partial per workgroup, trace_update_split(nt) per block
   L.gnp = take(sizeof(double) * d.nr * nvb * trace_update_split(d.nt));
@@ -169,7 +169,7 @@ struct mdd_plan {
   int n_gn() const { return (vs1() ? nblocks(d.nr) : d.nr * nvb) * trace_update_split(d.nt); }
   // Float64 loss partials written by one fused product launch over a batch of nb.
   int n_loss(int nb) const {
-    return d.nf * (vs1() ? gemv_groups(nb, d.nf) : gemm_loss_parts(d.precision, nb, nvb));
+    return d.nf * (vs1() ? gemv_groups(nb, d.nf, d.nr) : gemm_loss_parts(d.precision, nb, nvb));
   }
 
   template <class Fn>
@@ -233,16 +233,24 @@ struct mdd_plan {
     g.uns = streamed_data() ? d.nb_max : d.ns;
     g.upos = streamed_data() ? 1 : 0;
     if (vs1()) {
-      g.P = gemv_groups(nb, d.nf);
+      g.P = gemv_groups(nb, d.nf, d.nr);
       g.gpart = gvp();
     }
     return g;
   }
 
-  // Per-frequency products of one batch (any kind) on the plan's stream.
-  mdd_status products(int kind, const GemmArgs& g) {
+  // Per-frequency products of one batch (any kind) on the plan's stream.  A plan for one
+  // virtual source leaves an adjoint product that goes over R_k in its row-group partials,
+  // which the trace kernel `into` adds up as it reads them.
+  mdd_status products(int kind, const GemmArgs& g, TraceArgs* into = nullptr) {
+    const bool parts = vs1() && into && g.P > 1;
+    if (parts) {
+      into->gpart = g.gpart;
+      into->P = g.P;
+      into->npair = nrp / 2;
+    }
     return run(MDD_KC_GEMM, [&] {
-      return vs1() ? launch_gemv(kind, g, stream) : launch_gemm(kind, d.precision, g, stream);
+      return vs1() ? launch_gemv(kind, g, !parts, stream) : launch_gemm(kind, d.precision, g, stream);
     });
   }
 
@@ -254,23 +262,32 @@ struct mdd_plan {
     return run(MDD_KC_FFT_MODEL, [&] { return launch_trace(TM_RFFT, a, stream); });
   }
 
-  mdd_status reduce(const int32_t* idx, int nb, bool with_loss, double* loss_out,
-                    double* gnorm2_out) {
-    if (!loss_out && !gnorm2_out) return MDD_OK;
+  // The update (or gradient) kernel `mode` and the reduction of the batch's loss and of
+  // ||g||^2: in the kernel itself for few partials, else a launch of its own.
+  mdd_status update_and_reduce(int mode, TraceArgs& a, const int32_t* idx, int nb, double* loss_out,
+                               double* gnorm2_out) {
     ReduceArgs r{};
     r.loss_part = lossp();
-    r.n_loss = with_loss ? n_loss(nb) : 0;
+    r.n_loss = n_loss(nb);
     r.loss_scale = 1.0 / (2.0 * d.nt);
-    r.oob = with_loss ? oob() : nullptr;
+    r.oob = oob();
     r.idx = idx;
     r.nb = nb;
     r.ns = d.ns;
     r.oob_pos = streamed_data() ? 1 : 0;
     r.gn_part = gnp();
-    r.n_gn = gnorm2_out ? n_gn() : 0;
+    r.n_gn = n_gn();
     r.loss_out = loss_out;
     r.gnorm2_out = gnorm2_out;
     r.stage = red2();
+    a.part = gnp();
+    const bool wanted = loss_out || gnorm2_out, here = wanted && r.n_gn <= RED_IN_UPDATE;
+    if (here) {
+      a.red = r;
+      a.done = reinterpret_cast<unsigned*>(tw() + 2 * d.nt - 1);  // past the twiddle tables
+    }
+    MDD_TRY(run(MDD_KC_UPDATE, [&] { return launch_trace(mode, a, stream); }));
+    if (!wanted || here) return MDD_OK;
     return run(MDD_KC_REDUCE, [&] { return launch_reduce(r, stream); });
   }
 
@@ -533,8 +550,8 @@ mdd_status mdc_adjoint(mdd_plan* p, const float* V, const int32_t* idx, int32_t 
   a.x_in = V;
   MDD_TRY(p->run(MDD_KC_DATA_FFT, [&] { return launch_trace(TM_RFFT, a, p->stream); }));
   const GemmArgs g = p->gemm(idx, nb);
-  MDD_TRY(p->products(GK_ADJ, g));
   TraceArgs b = p->blocked(p->F(), p->d.nr);
+  MDD_TRY(p->products(GK_ADJ, g, &b));
   b.x_out = G_out;
   return p->run(MDD_KC_UPDATE, [&] { return launch_trace(TM_IRFFT, b, p->stream); });
 }
@@ -591,13 +608,11 @@ mdd_status mdd_stoch_grad(mdd_plan* p, const float* R, const int32_t* idx, int32
   p->spec_model = nullptr;
   MDD_TRY(p->model_fft(R, nullptr, 0.0));
   const GemmArgs g = p->gemm(idx, nb);
-  MDD_TRY(p->products(GK_FUSED, g));
   TraceArgs a = p->blocked(p->F(), p->d.nr);
+  MDD_TRY(p->products(GK_FUSED, g, &a));
   a.x_out = G_out;
   a.onset = p->mask_set ? p->onset() : nullptr;
-  a.part = p->gnp();
-  MDD_TRY(p->run(MDD_KC_UPDATE, [&] { return launch_trace(TM_GRAD, a, p->stream); }));
-  return p->reduce(idx, nb, true, loss_out, gnorm2_out);
+  return p->update_and_reduce(TM_GRAD, a, idx, nb, loss_out, gnorm2_out);
 }
 
 mdd_status mdd_step(mdd_plan* p, float* R, float* s0, float* s1, const mdd_opt* opt,
@@ -616,18 +631,17 @@ mdd_status mdd_step(mdd_plan* p, float* R, float* s0, float* s1, const mdd_opt* 
   p->spec_model = nullptr;
   if (!have) MDD_TRY(p->model_fft(R, vel, mu));
   const GemmArgs g = p->gemm(idx, nb);
-  MDD_TRY(p->products(GK_FUSED, g));
+  MDD_TRY(p->products(GK_FUSED, g, &a));
   a.model = R;
   a.store_spec = store ? 1 : 0;
   a.onset = p->mask_set ? p->onset() : nullptr;
-  a.part = p->gnp();
-  MDD_TRY(p->run(MDD_KC_UPDATE, [&] { return launch_trace(mode, a, p->stream); }));
+  MDD_TRY(p->update_and_reduce(mode, a, idx, nb, loss_out, gnorm2_out));
   if (store) {
     p->spec_model = R;
     p->spec_vel = vel;
     p->spec_mu = mu;
   }
-  return p->reduce(idx, nb, true, loss_out, gnorm2_out);
+  return MDD_OK;
 }
 
 mdd_status mdd_stoch_grad_noalloc(const mdd_dims* dims, const float* d, const float* u,
@@ -741,7 +755,7 @@ mdd_status mdd_calibrate_rows(const float* D, const int32_t* idx, float* out, in
   if (nb < 1 || nb > NB_LIMIT || ns < 1 || ns > MAX_STREAM_NS || nr < 1 || nr > MAX_EXTENT ||
       nf < 1 || nf > MAX_EXTENT / 2 + 1)
     return MDD_ESHAPE;
-  if (groups == 0) groups = gemv_groups(nb, nf);
+  if (groups == 0) groups = gemv_groups(nb, nf, nr);
   if (groups < 1 || groups > nb) return MDD_ESHAPE;
   return launch_calibrate_rows(reinterpret_cast<const float2*>(D), idx, reinterpret_cast<float2*>(out),
                                nb, nf, ns, static_cast<int>(round16(nr)), groups,

@@ -113,8 +113,8 @@ __device__ __forceinline__ void mac_conj(Left a, float2 b, float bsum, Tile& t) 
 
 // Adds a group's sum to the running total with the rounding error of that addition kept
 // (Kahan's compensated sum): the error goes in front of the next group's products, as
-// the value their accumulators start from.  Each group of 64 receivers starts near zero,
-// so the products' rounding grows with 64 and not with nr.
+// the value their accumulators start from.  Each group of 64 receivers (32 at up to 16 batch
+// rows) starts near zero, so the products' rounding grows with the group and not with nr.
 template <int PREC>
 __device__ __forceinline__ void fold(Tile& t, floatx4& re, floatx4& im) {
 #pragma unroll
@@ -134,7 +134,7 @@ template <int NBT>
 struct RowsCfg {
   static constexpr bool WIDE = NBT >= 2;          // left operands prepared in LDS (16 bytes each)
   static constexpr int KC = 32;                   // receivers per chunk
-  static constexpr int SUM = 64 / KC;             // chunks per compensated addition
+  static constexpr int SUM = NBT == 1 ? 1 : 64 / KC;  // chunks per compensated addition
   static constexpr int KS = KC / 4;               // k-steps per chunk
   static constexpr int MB = 16 * NBT;
   static constexpr int NBUF = 2;                // chunks of R_k in registers (a multiple of SUM)

@@ -64,7 +64,22 @@ struct TraceArgs {
   const int32_t* onset;   // [rows][ncols] or NULL
   double* part;           // per-tile float64 partial: out-of-band energy or ||g||^2
   const float2* tw;       // exp(-2 pi i m / nt), m < nt
+  // Gradient / update modes with one virtual source: the spectra to transform are the sum of
+  // P row-group partials [nf][P][npair] (receiver pairs), added as they are staged.
+  const float4* gpart;
+  int P, npair;
+  // Gradient / update modes: the launch does the reduction `red` as well (gn_part is `part`):
+  // a workgroup of its own the loss, the last of the others ||g||^2.  `done` counts them, 0
+  // before and after.  NULL: the reduction is another launch.
+  unsigned* done;
+  ReduceArgs red;
 };
+
+// Workgroups (gradient-norm partials) up to which the update kernel does the reduction: one
+// workgroup a CU, where it replaces a launch (a 32-trace step 15.8 -> 13.3 us).  With more,
+// each of them still waits for its partial and its count to arrive, one round after the
+// other: 2200 workgroups 50.6 -> 63.6 us a step, 5200 in the gradient kernel 196 -> 213 us.
+constexpr int RED_IN_UPDATE = 256;
 
 enum GemmKind : int {
   GK_FUSED = 0,   // Res = D_b R_k - U_b (loss partials); G_k = D_b^H Res, written over R_k
@@ -110,10 +125,11 @@ hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStrea
 constexpr int SPLIT_PIPE_KC = 256;
 hipError_t launch_gemm_split(int kind, int precision, const GemmArgs& a, hipStream_t s);
 // nvs = 1 products (gemv_kernels.hip): every kind, every precision, in float32; spectra
-// in the one-row layout.  a.P = gemv_groups(nb, nf) row groups per frequency; with P > 1
+// in the one-row layout.  a.P = gemv_groups(nb, nf, nr) row groups per frequency; with P > 1
 // the adjoint kinds take a second launch that adds the group partials.
-int gemv_groups(int nb, int nf);
-hipError_t launch_gemv(int kind, const GemmArgs& a, hipStream_t s);
+int gemv_groups(int nb, int nf, int nr);
+// with `sum` false the partials stay in a.gpart.
+hipError_t launch_gemv(int kind, const GemmArgs& a, bool sum, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_row_sum(const double* part, int rows, int cols, double scale, double* out,
                           hipStream_t s);

@@ -240,6 +240,42 @@ __device__ __forceinline__ double tile_sum(double v, double* red) {
   return s;
 }
 
+// The loss (see k_reduce for the sum), by a workgroup of its own beside the update's: the
+// partials are an earlier launch's.
+template <int NTH>
+__device__ __forceinline__ void loss_here(const ReduceArgs& r, double* red) {
+  const int tid = threadIdx.x;
+  double o = 0.0;
+  if (tid < r.nb && r.oob) {
+    const int s = r.idx[tid];
+    if (s >= 0 && s < r.ns) o = r.oob[r.oob_pos ? tid : s];
+  }
+  const double l = block_fixed_sum<NTH>(r.loss_part, r.n_loss, red);
+  o = wave_sum(o);  // nb <= 64: the first wavefront's
+  if (tid == 0 && r.loss_out) r.loss_out[0] = l * r.loss_scale + o;
+}
+
+// ||g||^2, by the launch's last workgroup: the partials were stored past the L2 caches (agent
+// scope) by workgroups on other XCDs and are read the same way.
+template <int NTH>
+__device__ __forceinline__ void norm_here(const ReduceArgs& r, const double* part, double* red) {
+  double g = 0.0;
+  int i = threadIdx.x;
+  auto at = [&](int j) {
+    return __hip_atomic_load(part + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  for (; i + 7 * NTH < r.n_gn; i += 8 * NTH) {
+    double x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = at(i + j * NTH);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) g += x[j];
+  }
+  for (; i < r.n_gn; i += NTH) g += at(i);
+  g = tile_sum<NTH / 64>(g, red);
+  if (threadIdx.x == 0 && r.gnorm2_out) r.gnorm2_out[0] = g;
+}
+
 // One workgroup per tile of CB traces, one wavefront per trace (or several
 // traces per wavefront for short traces).  Update modes request a trace's model
 // and optimiser state just before its inverse transform (the loads are in flight
@@ -256,15 +292,26 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
   float2* s_sc = smem + S::TW_SIZE;
   float2* s_spec = s_sc + NW * TPW * S::SC;
   __shared__ double s_red[NW];
+  __shared__ bool s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int p = lane / L, j = lane % L;
   // workgroup -> (tile, part): a group of 8 * SPLIT consecutive ids holds every
   // part of 8 tiles, ids w, w + 8, ... (one XCD under round-robin dispatch) the
   // parts of one tile.
-  int tile = blockIdx.x, half = 0;
+  int bid = blockIdx.x;
+  if constexpr (C::UPD) {
+    if (a.done) {  // the first workgroup reduces the loss
+      if (bid == 0) {
+        loss_here<NTH>(a.red, s_red);
+        return;
+      }
+      --bid;
+    }
+  }
+  int tile = bid, half = 0;
   if constexpr (C::SPLIT > 1) {
-    const int g = blockIdx.x / (8 * C::SPLIT), w = blockIdx.x % (8 * C::SPLIT);
+    const int g = bid / (8 * C::SPLIT), w = bid % (8 * C::SPLIT);
     const int m = min(8, a.rows * a.ncb - 8 * g);  // tiles in this group
     tile = 8 * g + w % m;
     half = w / m;
@@ -293,13 +340,39 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
     }
   };
 
+#pragma unroll 2
   for (int i = tid; i < S::TW_SIZE; i += NTH) s_tw[i] = a.tw[i];
   if (MODE != TM_RFFT) {
-    for (int i = tid; i < nf * (CW / 2); i += NTH) {
-      const int k = i / (CW / 2), c2 = 2 * (i % (CW / 2));
-      const float4 z = *reinterpret_cast<const float4*>(gspec + k * a.s_k + c2);
-      s_spec[k * SPS + c2] = make_float2(z.x, z.y);
-      s_spec[k * SPS + c2 + 1] = make_float2(z.z, z.w);
+    if (MODE != TM_RFFT && a.gpart) {
+      const int q0 = (cb * CB + half * CW) / 2;    // receiver pair of the tile's first column
+      for (int i = tid; i < nf * (CW / 2); i += NTH) {
+        const int k = i / (CW / 2), c = i % (CW / 2);
+        const float4* g = a.gpart + (long long)k * a.P * a.npair + min(q0 + c, a.npair - 1);
+        float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int p0 = 0; p0 < a.P; p0 += 4) {      // four partials requested at a time
+          float4 y[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[j] = g[(long long)min(p0 + j, a.P - 1) * a.npair];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (p0 + j >= a.P) break;
+            z.x += y[j].x;
+            z.y += y[j].y;
+            z.z += y[j].z;
+            z.w += y[j].w;
+          }
+        }
+        s_spec[k * SPS + 2 * c] = make_float2(z.x, z.y);
+        s_spec[k * SPS + 2 * c + 1] = make_float2(z.z, z.w);
+      }
+    } else {
+#pragma unroll 2
+      for (int i = tid; i < nf * (CW / 2); i += NTH) {
+        const int k = i / (CW / 2), c2 = 2 * (i % (CW / 2));
+        const float4 z = *reinterpret_cast<const float4*>(gspec + k * a.s_k + c2);
+        s_spec[k * SPS + c2] = make_float2(z.x, z.y);
+        s_spec[k * SPS + c2 + 1] = make_float2(z.z, z.w);
+      }
     }
   }
   __syncthreads();
@@ -458,7 +531,19 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
 
   if (a.part) {
     const double tot = tile_sum<NW>(part, s_red);
-    if (tid == 0) a.part[blockIdx.x] = tot;
+    if (tid == 0) {
+      if (C::UPD && a.done) {
+        // The partial has to be in memory before the count says so.  The store and the count
+        // are agent-scope accesses, which go past the XCD's L2, and the wait orders them: a
+        // release fence would write back the whole L2 (the update kernel took 1.05 ms so).
+        __hip_atomic_store(a.part + bid, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                 gridDim.x - 2;
+      } else {
+        a.part[bid] = tot;
+      }
+    }
   }
   if (MODE == TM_RFFT || (UPDATE && a.store_spec)) {
     __syncthreads();
@@ -468,11 +553,21 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
       *reinterpret_cast<float4*>(gspec + k * a.s_k + c2) = make_float4(z0.x, z0.y, z1.x, z1.y);
     }
   }
+  if constexpr (C::UPD) {
+    if (a.done) {
+      __syncthreads();
+      if (s_last) {
+        if (tid == 0) __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        norm_here<NTH>(a.red, a.part, s_red);
+      }
+    }
+  }
 }
 
 // Builds the twiddle table of FftShape for nt (float64 angles, rounded once).
 __global__ void k_twiddles(float2* tw, int nt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 2 * nt - 1) tw[i] = make_float2(0.f, 0.f);  // past the tables: the count of TraceArgs::done
   const int n2 = nt / 2;
   const int np8 = n2 >= 512 ? 3 : 2;
   const int rem = n2 / (np8 == 3 ? 512 : 64);
@@ -508,7 +603,7 @@ size_t trace_smem(int nf) {
 template <int NT, int MODE>
 hipError_t launch_mode(const TraceArgs& a, hipStream_t s) {
   using C = TraceCfg<NT, MODE>;
-  const dim3 grid(a.rows * a.ncb * C::SPLIT), block(C::THREADS);
+  const dim3 grid(a.rows * a.ncb * C::SPLIT + (C::UPD && a.done ? 1 : 0)), block(C::THREADS);
   const size_t sm = trace_smem<NT, MODE>(a.nf);
   if (sm > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_trace<NT, MODE>),

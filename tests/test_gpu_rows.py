@@ -71,3 +71,23 @@ def test_full_gradient_in_batches_of_64(prec, tol, ns, nvs):
     assert relerr(H(G), go) <= tol
     assert abs(loss.item() - lo) <= tol * lo
     assert abs(gn.item() - np.sum(go ** 2)) <= 2 * tol * np.sum(go ** 2)
+
+
+@pytest.mark.parametrize("nt", [128, 512, 1024])
+@pytest.mark.parametrize("nr,nvs,nb", [(8, 16, 4), (33, 35, 9), (100, 20, 7), (300, 1, 3), (300, 1, 40), (2000, 1, 17)])
+def test_loss_and_norm_of_repeated_steps(nt, nr, nvs, nb):
+    """The reductions at sizes where the update kernel's last workgroup does them and where a
+    launch of its own does, repeated on one plan: every call's loss and gradient norm."""
+    ns, nf = 45, 30
+    d, u, r = random_case(ns, nr, nvs, nt, seed=nr + nb)
+    plan = make_plan(d, u, nb_max=nb, nf=nf)
+    rng = np.random.default_rng(nt)
+    for _ in range(4):
+        idx = rng.integers(0, ns, size=nb).astype(np.int32)
+        lo, go = freq.batch_loss_grad(d, r, u, idx, nf)
+        G, loss, gn = plan.mdd_stoch_grad(T(r), T(idx, torch.int32))
+        assert relerr(H(G), go) <= TOL
+        assert abs(loss.item() - lo) <= TOL * lo
+        assert abs(gn.item() - np.sum(go ** 2)) <= 2 * TOL * np.sum(go ** 2)
+        v = f32(rng.standard_normal((nb, nvs, nt)))
+        assert relerr(H(plan.mdc_adjoint(T(v), T(idx, torch.int32))), freq.mdc_adjoint(d[idx], v, nf)) <= TOL
