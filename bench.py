@@ -738,11 +738,13 @@ def bench_autograd(args, dev):
            "achieved": rec_bytes / (rec_ms * 1e-3) / 1e9, "unit": "GB/s", "peak": HBM_PEAK_GBS,
            "frac": rec_bytes / (rec_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
     add_practical(rec, practical_hbm_gbs(dev), rec_ms)
-    # C_r on the spectra alone (the model spectra of one mdc_forward_rec), by the plan's events
+    # C_r on the spectra alone (the gradient spectra of one mdc_adjoint_rec at the largest batch;
+    # the other products take it in), by the plan's events
     plan.profile_enable(True, capacity=64)
     idx_last = idx_tab[0, :lens[0]]
+    v_last = u.index_select(0, idx_last.long())
     for _ in range(10):
-        plan.mdc_forward_rec(zz, idx_last)
+        plan.mdc_adjoint_rec(v_last, idx_last)
     srec = plan.profile_read()["reciprocity"]
     plan.profile_enable(False)
     srec_ms = srec[0] / max(srec[1], 1)

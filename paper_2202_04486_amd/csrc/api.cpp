@@ -573,8 +573,9 @@ mdd_status mdc_forward_rec(mdd_plan* p, const float* R, const int32_t* idx, int3
   if (!p->kernel_set) return MDD_ESTATE;
   p->spec_model = nullptr;
   MDD_TRY(p->model_fft(R, nullptr, 0.0));
-  MDD_TRY(spec_reciprocity(p));
-  const GemmArgs g = p->gemm(idx, nb);
+  GemmArgs g = p->gemm(idx, nb);
+  g.rec = !p->vs1() && gemm_rec(GK_FWD, p->d.precision, nb) ? 1 : 0;
+  if (!g.rec) MDD_TRY(spec_reciprocity(p));
   MDD_TRY(p->products(GK_FWD, g));
   TraceArgs a = p->blocked(p->Bsp(), nb);
   a.x_out = U_out;
@@ -591,9 +592,10 @@ mdd_status mdc_adjoint_rec(mdd_plan* p, const float* V, const int32_t* idx, int3
   TraceArgs a = p->blocked(p->Bsp(), nb);
   a.x_in = V;
   MDD_TRY(p->run(MDD_KC_DATA_FFT, [&] { return launch_trace(TM_RFFT, a, p->stream); }));
-  const GemmArgs g = p->gemm(idx, nb);
+  GemmArgs g = p->gemm(idx, nb);
+  g.rec = !p->vs1() && gemm_rec(GK_ADJ, p->d.precision, nb) ? 1 : 0;
   MDD_TRY(p->products(GK_ADJ, g));
-  MDD_TRY(spec_reciprocity(p));
+  if (!g.rec) MDD_TRY(spec_reciprocity(p));
   TraceArgs b = p->blocked(p->F(), p->d.nr);
   b.x_out = G_out;
   return p->run(MDD_KC_UPDATE, [&] { return launch_trace(TM_IRFFT, b, p->stream); });

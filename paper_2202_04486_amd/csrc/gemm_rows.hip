@@ -153,8 +153,21 @@ struct RowsCfg {
 };
 
 // ACC: the adjoint product is added to what Gout holds (a sum over batches).
-template <int PREC, int NBT, int KIND, bool ACC, bool RES, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NBT >= 3 ? 2 : NBT == 2 ? 3 : 5)))
+//
+// REC: with the reciprocity average C_r (nr = nvs) folded in, forward and adjoint kinds.
+//   Forward: the right operand is R_k + R_k^T, its mirrored entries read beside the direct
+//   ones; the result is halved, which is exact.
+//   Adjoint: (G + G^T)(r, v) = sum_b conj(D[b, r]) V[b, v] + V[b, r] conj(D[b, v]), the same
+//   product over twice the rows: D and conj(V) on the left (conj(V) staged beside D), V and
+//   conj(D) of this block's columns on the right.
+// Bound by traffic: the forward form reads R_k twice (the second time from the caches where
+// it can), the adjoint's doubled rows cost matrix work.  At 301 traces and 257 bins, with the
+// pass over the spectra that this saves (64 to 88 us; forward + adjoint, us):
+//   batch  8: 45 + 70, 49 + 70 -> 64, 53      batch 32: 67 + 80, 68 + 80 -> 87, 118
+//   batch 16: 46 + 70, 49 + 70 -> 69, 72      batch 64: 110 + 88 -> 140 (forward)
+template <int PREC, int NBT, int KIND, bool ACC, bool REC, bool RES, int NW>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(NBT >= 3 || (REC && NBT == 2 && KIND == GK_FWD) ? 2 : NBT == 2 || (REC && !RES) ? 3 : REC ? 4 : 5)))
 void k_gemm_rows(GemmArgs a, int nslot) {
   using C = RowsCfg<NBT>;
   using E = std::conditional_t<C::WIDE, Left, float2>;
@@ -162,6 +175,9 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   constexpr int NBUF = C::NBUF, NTH = 64 * NW;
   constexpr int FPT = MB * (KC / 2) / NTH;        // receiver pairs of a D chunk per thread
   static_assert(FPT * NTH == MB * (KC / 2), "split");
+  constexpr bool RFWD = REC && KIND == GK_FWD, RADJ = REC && KIND == GK_ADJ;
+  constexpr int HALF = RADJ ? MB / 2 : MB;        // rows of D; the others are conj(V)'s
+  static_assert(!REC || (PREC == MDD_PREC_FP32 && KIND != GK_FUSED), "reciprocity");
   extern __shared__ __align__(16) char s_raw[];
   E* const s_d = reinterpret_cast<E*>(s_raw);     // nslot chunks of D [row][receiver]
 
@@ -183,11 +199,13 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   const int nr = a.nr, nc = (nr + KC - 1) / KC;
 
   // R_k rows of a chunk -> registers (the right operand's layout: k-step q, lane quarter
-  // lq is receiver 4 q + lq of the chunk); rows at or past nr are out of bounds: zeros.
+  // lq is receiver rstep(q) + RQ lq of the chunk); rows at or past nr are out of bounds: zeros.
+  constexpr int RQ = RFWD ? 2 : 1;
+  auto rstep = [](int q) { return q / RQ * 4 * RQ + q % RQ; };
   const long long col = ((long long)blk * a.nf + k) * CB;
   unsigned roff[KS];
 #pragma unroll
-  for (int q = 0; q < KS; ++q) roff[q] = ((unsigned)(4 * q + lq) * rs32 + lr) * 8u;
+  for (int q = 0; q < KS; ++q) roff[q] = ((unsigned)(rstep(q) + RQ * lq) * rs32 + lr) * 8u;
   // The spectra of up to KC receivers from r0 on, seen from this block's column: what lies
   // past receiver nr is out of bounds (32 rows of at most 256 blocks x 513 bins fit 32 bits).
   auto rows_at = [&](float2* base, int r0, int rows) {
@@ -199,10 +217,49 @@ void k_gemm_rows(GemmArgs a, int nslot) {
 #pragma unroll
     for (int q = 0; q < KS; ++q) dst[q] = buffer_get2(rb, roff[q]);
   };
-  float2 rbuf[NBUF][KS];
+  // The forward product's order over the chunks.  With reciprocity at up to 16 batch rows it
+  // alternates around the workgroup's own columns: a mirrored entry is then a direct one of
+  // another workgroup's next or last chunk, and still in L2 (301 traces, 8 rows: 76 -> 67 us;
+  // with more rows fewer frequencies are under way at once and the order makes no difference).
+  const int c0 = blk0 * CB / KC;
+  auto ord = [&](int v) {
+    if constexpr (!RFWD || NBT > 1) return v;
+    const int c = c0 + ((v & 1) ? (v + 1) / 2 : nc - v / 2);
+    return v >= nc ? nc : c >= nc ? c - nc : c;
+  };
+  // The mirrored entries: column lr of this block as a row, RQ neighbouring receivers of the
+  // chunk as columns, zeros past receiver nr (what the padding columns of a block hold is not
+  // known to be finite).
+  unsigned toff[RFWD ? KS / 2 : 1];
+  if constexpr (RFWD) {
+#pragma unroll
+    for (int q = 0; q < KS / 2; ++q) {
+      const int r = rstep(2 * q) + RQ * lq;
+      toff[q] = ((unsigned)lr * rs32 + (unsigned)(r / CB * a.nf * CB + r % CB)) * 8u;
+    }
+  }
+  auto load_t = [&](float2 (&dst)[RFWD ? KS : 1], int c) {
+    if constexpr (RFWD) {
+      const int tb = c * (KC / CB), in_row = (tb * a.nf + k) * CB;
+      const int n = tb < a.nvb ? min(nr - blk * CB, CB) : 0;
+      const auto tr = buffer_at(a.F + blk * CB * rowstride + in_row,
+                                n ? (unsigned)n * rs32 * 8u - (unsigned)in_row * 8u : 0u);
+#pragma unroll
+      for (int q = 0; q < KS / 2; ++q) {
+        const int r = rstep(2 * q) + RQ * lq, left = nr - c * KC;
+        const float4 z = buffer_get4(tr, r < left ? toff[q] : PAST_END);
+        dst[2 * q] = make_float2(z.x, z.y);
+        dst[2 * q + 1] = r + 1 < left ? make_float2(z.z, z.w) : make_float2(0.f, 0.f);
+      }
+    }
+  };
+  float2 rbuf[NBUF][KS], tbuf[NBUF][RFWD ? KS : 1];
   if constexpr (KIND != GK_ADJ) {                 // in flight while the batch is looked up
 #pragma unroll
-    for (int i = 0; i < NBUF - 1; ++i) load_r(rbuf[i], i);
+    for (int i = 0; i < NBUF - 1; ++i) {
+      load_r(rbuf[i], ord(i));
+      load_t(tbuf[i], ord(i));
+    }
   }
 
   // Batch rows: lane b of every wavefront holds the source of batch entry b, or -1.
@@ -213,35 +270,46 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   }
   const int drow = src >= 0 ? drow_of(a, lane, src) : -1;
 
-  // The thread's receiver pairs of a D chunk; rows without a source and receivers past the
+  // The thread's receiver pairs of a chunk of D (or V); rows without a source and receivers past the
   // padded row are out of bounds: zeros.
   const char* dbase = reinterpret_cast<const char*>(a.Df + (long long)k * a.dns * a.nrp);
   const unsigned dbytes = (unsigned)a.dns * (unsigned)a.nrp * 8u;
+  static_assert(NTH / (KC / 2) == 16, "of_v");    // a thread's rows are 16 apart,
+  auto of_v = [&](int q) { return RADJ && 16 * q + 4 * wave >= HALF; };  // a wavefront's four
   unsigned doff[FPT];
 #pragma unroll
   for (int q = 0; q < FPT; ++q) {
-    const int i = tid + NTH * q;
-    const int row = __shfl(drow, i / (KC / 2), 64);
-    doff[q] = row >= 0 ? ((unsigned)row * (unsigned)a.nrp + 2u * (i % (KC / 2))) * 8u : PAST_END;
+    const int i = tid + NTH * q, rr = 2 * (i % (KC / 2));
+    const int b = i / (KC / 2) - (of_v(q) ? HALF : 0);
+    const int row = __shfl(drow, b, 64);
+    if (of_v(q))                                  // batch spectra [b][block of 16][k][16]
+      doff[q] = (((unsigned)b * a.nvb + rr / CB) * a.nf + k) * (CB * 8u) + (rr % CB) * 8u;
+    else
+      doff[q] = ((unsigned)row * (unsigned)a.nrp + rr) * 8u;
+    if (row < 0) doff[q] = PAST_END;
   }
   constexpr int DB = RES ? 8 : 1;                 // chunks of D requested at once
   float4 dv[DB][FPT];
   auto load_d = [&](int c, float4 (&d)[FPT]) {
     const auto db = buffer_at(dbase + (long long)c * KC * 8, dbytes - (unsigned)(c * KC) * 8u);
+    const auto vb = buffer_at(a.Bsp + (long long)c * (KC / CB) * a.nf * CB,
+                              RADJ ? (unsigned)(a.nb * a.nvb - c * (KC / CB)) * (unsigned)a.nf * (CB * 8u) : 0u);
     const int left_in_row = a.nrp - c * KC;
 #pragma unroll
     for (int q = 0; q < FPT; ++q)
-      d[q] = buffer_get4(db, 2 * ((tid + NTH * q) % (KC / 2)) < left_in_row ? doff[q] : PAST_END);
+      d[q] = buffer_get4(of_v(q) ? vb : db,
+                         2 * ((tid + NTH * q) % (KC / 2)) < left_in_row ? doff[q] : PAST_END);
   };
-  auto stage_d = [&](int c, const float4 (&d)[FPT]) {
-    E* slot = s_d + (RES ? c : c % nslot) * SLOT;
+  auto stage_d = [&](int i, const float4 (&d)[FPT]) {  // the i-th chunk of the LDS slots
+    E* slot = s_d + (RES ? i : i % nslot) * SLOT;
 #pragma unroll
     for (int q = 0; q < FPT; ++q) {
-      const int i = tid + NTH * q, b = i / (KC / 2), rr = 2 * (i % (KC / 2));
+      const int j = tid + NTH * q, b = j / (KC / 2), rr = 2 * (j % (KC / 2));
       float4 v = d[q];
       // used here and not before: hoisted above the step's products, the sums of left_of
       // would wait there for these loads and, in order, for every store before them
       asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+      if (of_v(q)) v = make_float4(v.x, -v.y, v.z, -v.w);
       E* p = slot + C::phys(b) * DP + rr;
       if constexpr (C::WIDE) {
         p[0] = left_of<PREC>(make_float2(v.x, v.y));
@@ -259,14 +327,14 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   // down for the adjoint, which finds the last nslot chunks still in LDS.
   constexpr bool FWD = KIND != GK_ADJ;
   const int v0 = FWD ? 0 : nc, v1 = KIND == GK_FWD ? nc : 2 * nc;
-  auto chunk_of = [&](int v) { return v < nc ? v : max(2 * nc - 1 - v, 0); };
+  auto chunk_of = [&](int v) { return v < nc ? ord(v) : max(2 * nc - 1 - v, 0); };
   auto staged_at = [&](int v) {                   // step v needs its chunk brought in
     return v < v1 && (v < nc || !FWD || v >= nc + nslot);
   };
   // End of step v: the next step's chunk goes to LDS, the one after that is requested.
   auto advance = [&](int v) {
     if constexpr (!RES) {
-      if (staged_at(v + 1)) stage_d(chunk_of(v + 1), dv[0]);
+      if (staged_at(v + 1)) stage_d(RFWD ? v + 1 : chunk_of(v + 1), dv[0]);
       load_d(chunk_of(v + 2), dv[0]);
       __syncthreads();
     }
@@ -280,10 +348,17 @@ void k_gemm_rows(GemmArgs a, int nslot) {
     for (int t = 0; t < NBT; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = t * 16 + lq * 4 + e;
+        const int i = t * 16 + lq * 4 + e, row = i < HALF ? i : i - HALF;
         const int s = __shfl(src, row, 64), rowc = min(row, a.nb - 1);
         if (s >= 0 && blk * CB + lr < a.nvs) okrow |= 1u << (4 * t + e);
-        if constexpr (KIND == GK_ADJ)
+        if constexpr (RADJ) {                     // V, or conj(D) of this block's columns
+          const int dr = max(__shfl(drow, row, 64), 0);
+          const float2* pv = a.Bsp + (((size_t)rowc * a.nvb + blk) * a.nf + k) * CB + lr;
+          const float2* pd = a.Df + ((long long)k * a.dns + dr) * a.nrp + blk * CB + lr;
+          const float2 z = *(i < HALF ? pv : pd);
+          upre[t][e] = make_float2(z.x, i < HALF ? z.y : -z.y);
+        }
+        else if constexpr (KIND == GK_ADJ)
           upre[t][e] = a.Bsp[(((size_t)rowc * a.nvb + blk) * a.nf + k) * CB + lr];
         else if constexpr (KIND == GK_FUSED)
           upre[t][e] = a.Uf[urow_off(a, k, rowc, max(s, 0)) + blk * CB + lr];
@@ -301,7 +376,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
         if (c0 + i < nc) stage_d(c0 + i, dv[i]);
     }
   } else {
-    stage_d(chunk_of(v0), dv[0]);
+    stage_d(RFWD ? 0 : chunk_of(v0), dv[0]);
     load_d(chunk_of(v0 + 1), dv[0]);
   }
   __syncthreads();
@@ -323,19 +398,20 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       const floatx4 z = {0.f, 0.f, 0.f, 0.f};
       re[t] = im[t] = acc[t].t1 = acc[t].t2 = acc[t].t3 = z;
     }
-    const E* dl = s_d + C::phys(lr) * DP + lq;
+    const E* dl = s_d + C::phys(lr) * DP + RQ * lq;
     // U: v modulo NBUF, which says whether step v begins or ends a group of SUM chunks
     auto step = [&](int v, auto U, float2 (&cur)[KS], float2 (&nxt)[KS]) {
-      load_r(nxt, v + NBUF - 1);
+      load_r(nxt, ord(v + NBUF - 1));
+      load_t(tbuf[(U + NBUF - 1) % NBUF], ord(v + NBUF - 1));
       // left operands G k-steps at a time, read from LDS one group ahead of their products
       constexpr int G = NBT >= 3 ? 1 : 2;
-      const E* dsl = dl + (RES ? v : v % nslot) * SLOT;
+      const E* dsl = dl + (RES ? ord(v) : v % nslot) * SLOT;
       E av[2][G][NBT];
       auto read_a = [&](int g) {
 #pragma unroll
         for (int q = 0; q < G; ++q)
 #pragma unroll
-          for (int t = 0; t < NBT; ++t) av[g & 1][q][t] = dsl[t * 16 * DP + 4 * (G * g + q)];
+          for (int t = 0; t < NBT; ++t) av[g & 1][q][t] = dsl[t * 16 * DP + rstep(G * g + q)];
       };
       read_a(0);
 #pragma unroll
@@ -344,7 +420,8 @@ void k_gemm_rows(GemmArgs a, int nslot) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-          const float2 bv = cur[G * g + q];
+          float2 bv = cur[G * g + q];
+          if constexpr (RFWD) bv = cadd(bv, tbuf[U][G * g + q]);
           const float bsum = bv.x + bv.y;
 #pragma unroll
           for (int t = 0; t < NBT; ++t) mac<PREC>(left(av[g & 1][q][t]), bv, bsum, acc[t], U % C::SUM == 0 && g + q == 0);
@@ -385,6 +462,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       if (!((okrow >> (4 * t + e)) & 1)) z = make_float2(0.f, 0.f);
       if constexpr (KIND == GK_FUSED) lpart += (double)z.x * z.x + (double)z.y * z.y;
       if constexpr (KIND == GK_FWD) {
+        if constexpr (REC) z = cscale(z, 0.5f);
         if (row < a.nb) a.Bsp[(((size_t)row * a.nvb + blk) * a.nf + k) * CB + lr] = z;
       }
       re[t][e] = z.x;
@@ -445,6 +523,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float2 z = make_float2(gr[e], gi[e]);
+        if constexpr (REC) z = cscale(z, 0.5f);
         if constexpr (ACC) z = cadd(z, old[e]);
         buffer_put2(gb, goff[e], z);
       }
@@ -468,12 +547,21 @@ hipError_t launch_nw(int kind, const GemmArgs& a, int nslot, hipStream_t s) {
     hipLaunchKernelGGL(kernel, grid, block, sm, s, a, nslot);
     return hipGetLastError();
   };
+  constexpr bool R3 = PREC == MDD_PREC_FP32;      // reciprocity: the three-product form only
   switch (kind) {
     case GK_FUSED:
-      return a.gacc ? go(k_gemm_rows<PREC, NBT, GK_FUSED, true, RES, NW>)
-                    : go(k_gemm_rows<PREC, NBT, GK_FUSED, false, RES, NW>);
-    case GK_FWD: return go(k_gemm_rows<PREC, NBT, GK_FWD, false, RES, NW>);
-    case GK_ADJ: return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, RES, NW>);
+      return a.gacc ? go(k_gemm_rows<PREC, NBT, GK_FUSED, true, false, RES, NW>)
+                    : go(k_gemm_rows<PREC, NBT, GK_FUSED, false, false, RES, NW>);
+    case GK_FWD:
+      if constexpr (R3) {
+        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_FWD, false, true, RES, NW>);
+      }
+      return go(k_gemm_rows<PREC, NBT, GK_FWD, false, false, RES, NW>);
+    case GK_ADJ:
+      if constexpr (R3) {
+        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, true, RES, NW>);
+      }
+      return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, false, RES, NW>);
     default: return hipErrorInvalidValue;
   }
 }
@@ -503,16 +591,22 @@ hipError_t launch_prec(int kind, const GemmArgs& a, hipStream_t s) {
   // with three against 45 us at 201 receivers and 16 rows)
   if (kind == GK_FUSED && a.nb <= 16 && a.nr <= 224)
     return launch_nbt<MDD_PREC_FP32_CGEMM, 1>(kind, a, s);
-  if (a.nb <= 16) return launch_nbt<PREC, 1>(kind, a, s);
-  if (a.nb <= 32) return launch_nbt<PREC, 2>(kind, a, s);
-  if (a.nb <= 48) return launch_nbt<PREC, 3>(kind, a, s);
+  const int rows = a.rec && kind == GK_ADJ ? 2 * a.nb : a.nb;
+  if (rows <= 16) return launch_nbt<PREC, 1>(kind, a, s);
+  if (rows <= 32) return launch_nbt<PREC, 2>(kind, a, s);
+  if (rows <= 48) return launch_nbt<PREC, 3>(kind, a, s);
   return launch_nbt<PREC, 4>(kind, a, s);
 }
 
 }  // namespace
 
+bool gemm_rec(int kind, int precision, int nb) {
+  return precision == MDD_PREC_FP32 && (kind == GK_FWD || (kind == GK_ADJ && nb <= 32));
+}
+
 hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStream_t s) {
   if (a.nb <= 0 || a.nb > NB_LIMIT) return hipErrorInvalidValue;
+  if (a.rec && (a.nr != a.nvs || !gemm_rec(kind, precision, a.nb))) return hipErrorInvalidValue;
   return precision == MDD_PREC_FP32 ? launch_prec<MDD_PREC_FP32>(kind, a, s)
                                     : launch_prec<MDD_PREC_FP32_CGEMM>(kind, a, s);
 }

@@ -97,6 +97,7 @@ struct GemmArgs {
   const float* dmax;      // [nf] largest |Re|, |Im| of D_k (fp16 split forms; else NULL)
   float2* Gout;           // adjoint product destination (same layout as F); NULL: over R_k in F
   int gacc;               // 1: add the adjoint product to Gout instead of writing it
+  int rec;                // 1: the product of, or followed by, the reciprocity average (gemm_rec)
   int ns, nr, nrp, nvs, nvsp, nvb, nf, nt, nb;
   // Rows of D per frequency in Df (ns, or nb_max for staged batch rows) and where batch
   // entry b finds its row: 0 = row idx[b] (resident spectra), 1 = row b (staged).
@@ -120,6 +121,10 @@ int gemm_loss_parts(int precision, int nb, int nvb);
 // Float32 products (gemm_rows.hip): every kind and batch size; the fused kind writes nf *
 // nvb loss partials.
 hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStream_t s);
+// Whether the kind takes the reciprocity average in (GemmArgs::rec): the three-product
+// float32 form, forward, and adjoint up to 32 rows (beyond, the doubled rows would need more
+// than four blocks of 16; at 32 already 118 us against 68 + 80 us with a pass of its own).
+bool gemm_rec(int kind, int precision, int nb);
 // bf16x3 / fp16x3 products (gemm_split.hip): 16 < nb <= NB_LIMIT, or the fused kind
 // at nb <= 16 over at most SPLIT_PIPE_KC receivers (persistent kernel).
 constexpr int SPLIT_PIPE_KC = 256;

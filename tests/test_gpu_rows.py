@@ -91,3 +91,29 @@ def test_loss_and_norm_of_repeated_steps(nt, nr, nvs, nb):
         assert abs(gn.item() - np.sum(go ** 2)) <= 2 * TOL * np.sum(go ** 2)
         v = f32(rng.standard_normal((nb, nvs, nt)))
         assert relerr(H(plan.mdc_adjoint(T(v), T(idx, torch.int32))), freq.mdc_adjoint(d[idx], v, nf)) <= TOL
+
+
+@pytest.mark.parametrize("nb", [1, 8, 9, 16, 17, 24, 25, 32, 33, 48, 64])
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 48, 65, 321])
+def test_products_with_reciprocity(n, nb):
+    """The average in the products: row blocks shared by the two halves of the adjoint, mirrored
+    entries of ragged chunks.  What an earlier call with a model that is not finite left in the
+    plan's spectra must not come through."""
+    ns, nt, nf = 66, 128, 33
+    d, u, r = random_case(ns, n, n, nt, seed=n + nb)
+    rng = np.random.default_rng(nb)
+    idx = rng.integers(0, ns, size=nb).astype(np.int32)
+    if nb > 4:
+        idx[1], idx[nb - 1] = -1, ns
+    plan = make_plan(d, u, nb_max=nb, nf=nf)
+    good = (idx >= 0) & (idx < ns)
+    keep, ti = idx[good], T(idx, torch.int32)
+    plan.mdd_stoch_grad(torch.full((n, n, nt), np.inf, device="cuda"), ti)
+    mean = lambda z: 0.5 * (z + np.swapaxes(z, 0, 1))
+    ug = H(plan.mdc_forward_rec(T(r), ti))
+    assert relerr(ug[good], freq.mdc(d[keep], mean(r.astype(np.float64)), nf)) <= TOL
+    assert not ug[~good].any()
+    v = f32(rng.standard_normal((nb, n, nt)))
+    v[~good] = np.nan
+    ga = H(plan.mdc_adjoint_rec(T(v), ti))
+    assert relerr(ga, mean(freq.mdc_adjoint(d[keep], v[good], nf))) <= TOL
