@@ -169,7 +169,7 @@ struct mdd_plan {
   int n_gn() const { return (vs1() ? nblocks(d.nr) : d.nr * nvb) * trace_update_split(d.nt); }
   // Float64 loss partials written by one fused product launch over a batch of nb.
   int n_loss(int nb) const {
-    return d.nf * (vs1() ? gemv_groups(nb, d.nf, d.nr) : gemm_loss_parts(d.precision, nb, nvb));
+    return d.nf * (vs1() ? gemv_groups(nb, d.nf, d.nr) : nvb);
   }
 
   template <class Fn>

@@ -28,34 +28,26 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Deterministic block sum of one double per thread (blockDim.x == 256);
-// `red` is LDS of at least 4 doubles.  The result is valid in thread 0.
-// Adjoint-product output at element `off` of the spectra layout: written over R_k
-// in F (Gout NULL), or into Gout, or added to Gout (gacc: a sum over batches).
-template <class GemmArgsT>
-__device__ __forceinline__ void store_g(const GemmArgsT& a, long long off, float2 v) {
-  float2* p = (a.Gout ? a.Gout : a.F) + off;
-  if (a.gacc) v = cadd(v, *p);
-  *p = v;
+// Global memory through buffer descriptors: a uniform base, a 32-bit byte offset per lane
+// that does not change over a loop, and the hardware's bounds check, which reads zeros
+// past the end and drops stores there.  That takes the address arithmetic, the clamping
+// and the zeroing of partial chunks out of the vector unit.
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+constexpr unsigned PAST_END = 0xffffffffu;        // an offset that is out of bounds for every buffer
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
-
-// Streaming (non-temporal) accesses for data a launch touches once, R_k read and G
-// written by the product kernels, so that they do not evict the kernel rows D_b, which
-// every column group of a frequency reads again.
-typedef float stream_f4 __attribute__((ext_vector_type(4)));
-typedef float stream_f2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float4 stream_load4(const float2* p) {
-  const stream_f4 v = __builtin_nontemporal_load(reinterpret_cast<const stream_f4*>(p));
-  return make_float4(v[0], v[1], v[2], v[3]);
+__device__ __forceinline__ float2 buffer_get2(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
 }
-// store_g for the plain case (written over R_k in F) as a streaming store.
-template <class GemmArgsT>
-__device__ __forceinline__ void store_g_stream(const GemmArgsT& a, long long off, float2 v) {
-  if (a.gacc || a.Gout) {
-    store_g(a, off, v);
-  } else {
-    __builtin_nontemporal_store(stream_f2{v.x, v.y}, reinterpret_cast<stream_f2*>(a.F + off));
-  }
+__device__ __forceinline__ float4 buffer_get4(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+// NT: a streaming store, for results that push reused data out of the caches.
+template <bool NT = false>
+__device__ __forceinline__ void buffer_put2(__amdgpu_buffer_rsrc_t r, unsigned off, float2 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), r, off, 0, NT ? 2 : 0);
 }
 
 // Row of D_k for batch entry b whose source s is valid: s in the resident spectra,
@@ -70,17 +62,6 @@ __device__ __forceinline__ int drow_of(const GemmArgsT& a, int b, int s) {
 template <class GemmArgsT>
 __device__ __forceinline__ long long urow_off(const GemmArgsT& a, int k, int b, int s) {
   return ((long long)k * a.uns + (a.upos ? b : s)) * a.nvsp;
-}
-
-__device__ __forceinline__ double block_sum256(double v, double* red) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x == 0) s = ((red[0] + red[1]) + red[2]) + red[3];
-  return s;
 }
 
 // Sum of n doubles by one workgroup of NTH threads in a fixed order (four

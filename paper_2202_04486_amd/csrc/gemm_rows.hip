@@ -41,26 +41,6 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Global memory through buffer descriptors: a uniform base, a 32-bit byte offset per lane
-// that does not change over a loop, and the hardware's bounds check, which reads zeros
-// past the end and drops stores there.  That takes the address arithmetic, the clamping
-// and the zeroing of partial chunks out of the vector unit.
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-constexpr unsigned PAST_END = 0xffffffffu;        // an offset that is out of bounds for every buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ float2 buffer_get2(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-__device__ __forceinline__ float4 buffer_get4(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ void buffer_put2(__amdgpu_buffer_rsrc_t r, unsigned off, float2 v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), r, off, 0, 0);
-}
-
 // Left operand of one lane, z = x + i y, prepared once when D is staged, because a vector
 // addition between two products holds up the float32 matrix unit for about six cycles
 // whatever the occupancy (in a loop of 16x16x4 products alone 155 TFLOP/s; with four
@@ -604,11 +584,14 @@ bool gemm_rec(int kind, int precision, int nb) {
   return precision == MDD_PREC_FP32 && (kind == GK_FWD || (kind == GK_ADJ && nb <= 32));
 }
 
-hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStream_t s) {
+hipError_t launch_gemm(int kind, int precision, const GemmArgs& a, hipStream_t s) {
   if (a.nb <= 0 || a.nb > NB_LIMIT) return hipErrorInvalidValue;
   if (a.rec && (a.nr != a.nvs || !gemm_rec(kind, precision, a.nb))) return hipErrorInvalidValue;
-  return precision == MDD_PREC_FP32 ? launch_prec<MDD_PREC_FP32>(kind, a, s)
-                                    : launch_prec<MDD_PREC_FP32_CGEMM>(kind, a, s);
+  switch (precision) {
+    case MDD_PREC_FP32: return launch_prec<MDD_PREC_FP32>(kind, a, s);
+    case MDD_PREC_FP32_CGEMM: return launch_prec<MDD_PREC_FP32_CGEMM>(kind, a, s);
+    default: return launch_gemm_split(kind, precision, a, s);
+  }
 }
 
 }  // namespace mdd

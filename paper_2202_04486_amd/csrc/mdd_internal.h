@@ -115,20 +115,14 @@ hipError_t launch_trace(int mode, const TraceArgs& a, hipStream_t s);
 // Workgroups per 16-column block in the gradient / update modes at this nt; each
 // writes one float64 partial, so those launches write rows * ncb * split partials.
 int trace_update_split(int nt);
+// Products of every kind, precision and batch size (gemm_rows.hip; the split and bf16 forms
+// in gemm_split.hip); the fused kind writes nf * nvb float64 loss partials.
 hipError_t launch_gemm(int kind, int precision, const GemmArgs& a, hipStream_t s);
-// Float64 loss partials per frequency that the fused kind of launch_gemm writes.
-int gemm_loss_parts(int precision, int nb, int nvb);
-// Float32 products (gemm_rows.hip): every kind and batch size; the fused kind writes nf *
-// nvb loss partials.
-hipError_t launch_gemm_rows(int kind, int precision, const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_split(int kind, int precision, const GemmArgs& a, hipStream_t s);
 // Whether the kind takes the reciprocity average in (GemmArgs::rec): the three-product
 // float32 form, forward, and adjoint up to 32 rows (beyond, the doubled rows would need more
 // than four blocks of 16; at 32 already 118 us against 68 + 80 us with a pass of its own).
 bool gemm_rec(int kind, int precision, int nb);
-// bf16x3 / fp16x3 products (gemm_split.hip): 16 < nb <= NB_LIMIT, or the fused kind
-// at nb <= 16 over at most SPLIT_PIPE_KC receivers (persistent kernel).
-constexpr int SPLIT_PIPE_KC = 256;
-hipError_t launch_gemm_split(int kind, int precision, const GemmArgs& a, hipStream_t s);
 // nvs = 1 products (gemv_kernels.hip): every kind, every precision, in float32; spectra
 // in the one-row layout.  a.P = gemv_groups(nb, nf, nr) row groups per frequency; with P > 1
 // the adjoint kinds take a second launch that adds the group partials.

@@ -117,3 +117,62 @@ def test_products_with_reciprocity(n, nb):
     v[~good] = np.nan
     ga = H(plan.mdc_adjoint_rec(T(v), ti))
     assert relerr(ga, mean(freq.mdc_adjoint(d[keep], v[good], nf))) <= TOL
+
+
+# Bound per product and operand pair, relative to the norm: float32 spectra as above plus, for
+# bf16x3, the rounding of two low halves and the dropped low * low term (3 * 2^-18); for
+# fp16x3 the same at 2^-22; for bf16 the rounding of the two operands (2 * 2^-9).  The gradient
+# and the loss go through a residual of such products: twice that.
+SPLIT_TOL = {"bf16x3": TOL + 3 * 2.0 ** -18, "fp16x3": TOL + 3 * 2.0 ** -22, "bf16": TOL + 2.0 ** -8}
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "fp16x3", "bf16"])
+@pytest.mark.parametrize("nb,nr,nvs", [(1, 1, 2), (3, 33, 17), (16, 32, 65), (16, 321, 33), (17, 95, 64),
+                                       (32, 64, 130), (33, 63, 18), (48, 65, 66), (49, 129, 20),
+                                       (64, 40, 81)])
+def test_every_split_kind_at_tile_edges(prec, nb, nr, nvs):
+    ns, nt, nf, tol = 70, 128, 41, SPLIT_TOL[prec]
+    d, u, r = random_case(ns, nr, nvs, nt, seed=nb + nr + nvs)
+    rng = np.random.default_rng(nb)
+    idx = rng.integers(0, ns, size=nb).astype(np.int32)
+    if nb > 4:
+        idx[1], idx[nb - 1] = -1, ns
+        idx[3] = idx[2]
+    plan = make_plan(d, u, nb_max=nb, nf=nf, precision=prec)
+    good = (idx >= 0) & (idx < ns)
+    keep, ti = idx[good], T(idx, torch.int32)
+    plan.mdd_stoch_grad(torch.full((nr, nvs, nt), np.inf, device="cuda"), ti)  # leaves nothing behind
+    out = torch.full((nb, nvs, nt), np.nan, device="cuda")
+    ug = H(plan.mdc_forward(T(r), ti, out=out))
+    assert relerr(ug[good], freq.mdc(d[keep], r, nf)) <= tol
+    assert not ug[~good].any()
+    v = f32(rng.standard_normal((nb, nvs, nt)))
+    v[~good] = np.nan
+    ga = H(plan.mdc_adjoint(T(v), ti))
+    assert relerr(ga, freq.mdc_adjoint(d[keep], v[good], nf)) <= tol
+    G, loss, gn = plan.mdd_stoch_grad(T(r), ti)
+    lo, go = freq.batch_loss_grad(d, r, u, keep, nf)
+    assert relerr(H(G), go) <= 2 * tol
+    assert abs(loss.item() - lo) <= 2 * tol * lo
+    assert abs(gn.item() - np.sum(go ** 2)) <= 4.1 * tol * np.sum(go ** 2)
+    first = G.clone()
+    for _ in range(4):
+        assert torch.equal(plan.mdd_stoch_grad(T(r), ti)[0], first)
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "fp16x3"])
+@pytest.mark.parametrize("nf,nvs", [(63, 250), (64, 250), (33, 17)])
+@pytest.mark.parametrize("nb,nr", [(9, 31), (20, 33), (40, 65), (64, 97)])
+def test_split_products_with_few_and_many_workgroups(prec, nf, nvs, nb, nr):
+    """Both sides of 256 workgroups (four column blocks each): one or two wavefronts per block,
+    with odd and even numbers of receiver chunks."""
+    ns, nt, tol = 70, 128, SPLIT_TOL[prec]
+    d, u, r = random_case(ns, nr, nvs, nt, seed=nb + nr)
+    idx = np.random.default_rng(nb).integers(0, ns, size=nb).astype(np.int32)
+    plan = make_plan(d, u, nb_max=nb, nf=nf, precision=prec)
+    ti = T(idx, torch.int32)
+    assert relerr(H(plan.mdc_forward(T(r), ti)), freq.mdc(d[idx], r, nf)) <= tol
+    G, loss, _ = plan.mdd_stoch_grad(T(r), ti)
+    lo, go = freq.batch_loss_grad(d, r, u, idx, nf)
+    assert relerr(H(G), go) <= 2 * tol
+    assert abs(loss.item() - lo) <= 2 * tol * lo
