@@ -320,23 +320,34 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256) void k_sigma_pass(const float2* 
   }
 }
 
-// Largest |Re| or |Im| of D_k over all sources and receivers, per frequency (the
-// fp16 split forms scale D_{b,k} by a power of two derived from it).  One
-// workgroup per frequency; a maximum does not depend on the order.
-// Largest |Re|, |Im| of the first `count` entries of each frequency's block (blocks
-// `stride` entries apart).
-__global__ __launch_bounds__(256) void k_freq_absmax(const float2* Df, long long count,
-                                                     long long stride, float* out) {
-  const float2* x = Df + (long long)blockIdx.x * stride;
-  const long long per_freq = count;
+// Largest |Re| or |Im| of D_k over all sources and receivers, per frequency (the fp16 split
+// form scales D_{b,k} by a power of two derived from it): of the first `count` entries of
+// each frequency's block (blocks `stride` entries apart, both even).  One workgroup per
+// frequency, whose memory latency is what bounds it on a staged batch: sixteen wavefronts
+// with four 16-byte loads in flight each (48 rows of 400, 200 bins: with four wavefronts
+// and one 8-byte load 21 us, now 8 us).  A maximum does not depend on the order.
+constexpr int ABSMAX_THREADS = 1024;
+__global__ __launch_bounds__(ABSMAX_THREADS) void k_freq_absmax(const float2* Df, long long count,
+                                                                long long stride, float* out) {
+  const float4* x = reinterpret_cast<const float4*>(Df + (long long)blockIdx.x * stride);
+  const long long n = count / 2;
+  auto amax = [](float4 v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); };
   float m = 0.f;
-  for (long long i = threadIdx.x; i < per_freq; i += 256) m = fmaxf(m, fmaxf(fabsf(x[i].x), fabsf(x[i].y)));
+  long long i = threadIdx.x;
+  for (; i + 3 * ABSMAX_THREADS < n; i += 4 * ABSMAX_THREADS) {
+    const float4 a = x[i], b = x[i + ABSMAX_THREADS], c = x[i + 2 * ABSMAX_THREADS], d = x[i + 3 * ABSMAX_THREADS];
+    m = fmaxf(fmaxf(m, fmaxf(amax(a), amax(b))), fmaxf(amax(c), amax(d)));
+  }
+  for (; i < n; i += ABSMAX_THREADS) m = fmaxf(m, amax(x[i]));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  __shared__ float s_m[4];
+  __shared__ float s_m[ABSMAX_THREADS / 64];
   if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) out[blockIdx.x] = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < ABSMAX_THREADS / 64; ++w) m = fmaxf(m, s_m[w]);
+    out[blockIdx.x] = m;
+  }
 }
 
 // C_r z = (z + z^T) / 2 over the first two axes of [n][n][nt]: the workgroup of
@@ -438,7 +449,7 @@ hipError_t launch_iota(int32_t* out, int n, hipStream_t s) {
 
 hipError_t launch_freq_absmax(const float2* Df, int nf, long long count, long long stride,
                               float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_freq_absmax, dim3(nf), dim3(256), 0, s, Df, count, stride, out);
+  hipLaunchKernelGGL(k_freq_absmax, dim3(nf), dim3(ABSMAX_THREADS), 0, s, Df, count, stride, out);
   return hipGetLastError();
 }
 

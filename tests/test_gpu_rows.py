@@ -176,3 +176,17 @@ def test_split_products_with_few_and_many_workgroups(prec, nf, nvs, nb, nr):
     lo, go = freq.batch_loss_grad(d, r, u, idx, nf)
     assert relerr(H(G), go) <= 2 * tol
     assert abs(loss.item() - lo) <= 2 * tol * lo
+
+
+@pytest.mark.parametrize("s,r", [(0, 0), (85, 40), (149, 89), (136, 63)])
+def test_fp16_scale_finds_the_largest_entry_anywhere(s, r):
+    """One trace 2^20 times the others: were it missed in the scale, its halves would overflow."""
+    ns, nr, nvs, nt, nf = 150, 90, 20, 128, 30
+    d, u, m = random_case(ns, nr, nvs, nt, seed=s)
+    d[s, r] *= 2.0 ** 20
+    plan = make_plan(d, u, nb_max=8, nf=nf, precision="fp16x3")
+    idx = np.array([s, (s + 1) % ns], dtype=np.int32)
+    G, loss, _ = plan.mdd_stoch_grad(T(m), T(idx, torch.int32))
+    lo, go = freq.batch_loss_grad(d, m, u, idx, nf)
+    assert relerr(H(G), go) <= 2 * SPLIT_TOL["fp16x3"]
+    assert abs(loss.item() - lo) <= 2 * SPLIT_TOL["fp16x3"] * lo
