@@ -172,10 +172,10 @@ mdd_status mdc_adjoint(mdd_plan* plan, const float* V, const int32_t* idx, int32
 /* The same operators with the reciprocity preconditioner C_r of the preconditioned
  * functional (Theory section; C_r R = (R + R^T) / 2 over receiver and virtual source):
  *   mdc_forward_rec: U_out = P+_b C_r R;    mdc_adjoint_rec: G_out = C_r P+_b^H V.
- * C_r is applied to the retained spectra of R (after its transform) or of the adjoint
- * product (before the inverse transform), which equals applying it to the traces since
- * the transform acts on each trace alone; it reads and writes nr * nvs * nf complex
- * values instead of the traces.  Needs nr == nvs (MDD_ESHAPE otherwise) and
+ * C_r acts on the retained spectra of R or of the adjoint product, which equals applying
+ * it to the traces since the transform acts on each trace alone.  In MDD_PREC_FP32 it is
+ * part of the product (forward, and adjoint up to 32 rows); otherwise a pass over nr * nvs *
+ * nf complex values.  Needs nr == nvs (MDD_ESHAPE otherwise) and
  * mdd_set_kernel; arguments, layouts and errors as for mdc_forward / mdc_adjoint. */
 mdd_status mdc_forward_rec(mdd_plan* plan, const float* R, const int32_t* idx, int32_t nb,
                            float* U_out);
@@ -304,7 +304,7 @@ mdd_status mdd_sigma_max2(mdd_plan* plan, int32_t iters, double* lam_out);
 #define MDD_KC_UPDATE 2      /* inverse transform + mask + update (+ model transform) */
 #define MDD_KC_REDUCE 3      /* float64 reductions */
 #define MDD_KC_DATA_FFT 4    /* transforms of batch data (forward / adjoint operators) */
-#define MDD_KC_RECIPROCITY 5 /* C_r on spectra (mdc_forward_rec / mdc_adjoint_rec) */
+#define MDD_KC_RECIPROCITY 5 /* C_r on spectra, where it is a pass of its own */
 #define MDD_KC_COUNT 6
 mdd_status mdd_profile_enable(mdd_plan* plan, int32_t enable, int32_t capacity);
 mdd_status mdd_profile_read(mdd_plan* plan, double* ms_host, int64_t* count_host);
@@ -333,7 +333,7 @@ mdd_status mdd_calibrate_update(float* R, float* s0, float* s1, float* spec, int
  * into groups of ceil(nb / groups)) but none of their arithmetic, reductions or
  * barriers, and writes one partial per (frequency, group, receiver pair) to out
  * (nf * groups * round16(nr) / 2 float4).  Its duration is the floor of that access
- * pattern.  groups 0 takes the number the products kernel uses for (nb, nf).  Pointers
+ * pattern.  groups 0 takes the number the products kernel uses for (nb, nf, nr).  Pointers
  * D and out 16-byte aligned; enqueued on `stream`.  Errors: EINVAL (NULL, misaligned),
  * ESHAPE (nb outside [1, 64], ns outside [1, 2^20], nr outside [1, 4096], nf outside
  * [1, 2049], groups outside [1, nb]), EHIP. */
