@@ -315,8 +315,8 @@ void k_gemm_split(GemmArgs a) {
   // For the adjoint: a lane takes one receiver and eight rows, 4 lq .. 4 lq + 3 of tiles 2 w'
   // and 2 w' + 1 (zeros where the second is past the batch); the left operand is conj(D),
   // whose negated imaginary part is Im D.  A half-empty k-step keeps the 16x16x32 shape:
-  // with 16x16x16 products at the end of the same sums the first two result registers were
-  // read before they were complete in one of the instances (wrong by 1e-4, fp16, 48 rows).
+  // with 16x16x16 products at the end of the same sums, two of a tile's four result registers
+  // were wrong by 1e-4 in one of the instances (fp16, 48 rows).
   const int akk = wave >> 1, ar = 16 * (wave & 1) + lr;
   unsigned aoff[8];
 #pragma unroll
