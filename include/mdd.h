@@ -72,7 +72,10 @@ typedef int32_t mdd_status;
                              from three real ones, except in the fused gradient / step at
                              most 16 batch rows over at most 224 receivers, which uses four */
 #define MDD_PREC_BF16X3 1 /* bf16 hi+lo split, hi*hi + hi*lo + lo*hi, float32 accumulate */
-#define MDD_PREC_FP16X3 2 /* fp16 hi+lo split with power-of-two tile scaling, float32 accumulate */
+#define MDD_PREC_FP16X3 2 /* fp16 hi+lo split with power-of-two scales, float32 accumulate.  D's
+                             scales are taken per batch row and per receiver at up to 16 batch
+                             rows; with more, one per frequency from its largest entry over all
+                             sources, so that rows 2^-14 of it and below lose bits */
 #define MDD_PREC_BF16 3   /* single bf16 product (diagnostic: expected to miss 1e-3) */
 #define MDD_PREC_FP32_CGEMM 4 /* float32 with four real products per complex one everywhere,
                                  as a plain complex GEMM does (a comparison form) */

@@ -17,8 +17,11 @@
 // forward product as [row][receiver], for the adjoint as [receiver][row] in the order
 // above, so that each operand is one 16-byte LDS read per plane (re hi, re lo, and hi, lo of
 // the negated imaginary part).  fp16 carries power-of-two scales so that the low halves stay
-// normal: one per frequency for D_{b,k} (from its largest |D|, found when the kernel is
-// set), and one per column for each receiver chunk of R_k and for the residual.
+// normal: one per column for each receiver chunk of R_k and for the residual, and for
+// D_{b,k} at up to 16 batch rows one per batch row (forward) and per receiver (adjoint) of a
+// chunk, found while it is staged, so that weak sources keep their bits beside a strong one;
+// with more rows one per frequency (from the largest |D| of all sources, found when the kernel
+// is set).
 //
 // What bounds it: the traffic of R_k and G_k in pieces of 16 columns (128 bytes, a whole
 // spectra row apart), 3.4 to 3.9 TB/s for the forward and adjoint kinds alone; the bf16 form,
@@ -101,16 +104,14 @@ __device__ __forceinline__ void cmma_hi(const V (&a)[4], const V& brh, const V& 
   re = T::mma(a[2], bih, re);
 }
 
-// Power-of-two scale bringing max |x| to [2^13, 2^14), and its inverse; the
-// exponent is clamped so that both stay finite.
+// Power-of-two scale bringing max |x| to [2^13, 2^14), and its inverse, from the exponent
+// bits; clamped so that both stay finite (1 where the maximum is not).  A zero maximum takes
+// the largest scale, which its zeros ignore.
 __device__ __forceinline__ float2 pow2_scale_pair(float amax) {
-  if (!(amax > 0.f) || !(amax < 3.0e38f)) return make_float2(1.f, 1.f);
-  int e;
-  frexpf(amax, &e);  // amax = m 2^e, m in [0.5, 1)
-  const int sh = min(max(14 - e, -120), 120);
-  return make_float2(ldexpf(1.f, sh), ldexpf(1.f, -sh));
+  const int e = __float_as_int(amax) >> 23;  // amax = m 2^(e - 126), m in [0.5, 1)
+  const int sh = e == 255 ? 0 : min(140 - e, 120);
+  return make_float2(__int_as_float((127 + sh) << 23), __int_as_float((127 - sh) << 23));
 }
-
 
 template <int PREC, typename V>
 __device__ __forceinline__ void split8(const float (&x)[8], V& hi, V& lo) {
@@ -157,6 +158,20 @@ struct SplitCfg {
   static constexpr int SLOT = 4 * (FPL > APL ? FPL : APL);        // elements per chunk of D
   static constexpr size_t SMEM = 2 * 2 * (size_t)SLOT;            // two chunks of 2-byte elements
 };
+
+// Largest magnitude among 8 complex values (a tree: it is in the way of their use).
+__device__ __forceinline__ float amax8(const float (&x)[8], const float (&y)[8]) {
+  float m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    m[i] = fmaxf(fmaxf(fabsf(x[2 * i]), fabsf(y[2 * i])), fmaxf(fabsf(x[2 * i + 1]), fabsf(y[2 * i + 1])));
+  return fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+}
+// Maximum over four neighbouring lanes.
+__device__ __forceinline__ float quad_max(float m) {
+  m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0xb1, 0xf, 0xf, false)));  // 1, 0, 3, 2
+  return fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x4e, 0xf, 0xf, false)));  // 2, 3, 0, 1
+}
 
 // Eight values of a row (or receiver): real parts x and the negated imaginary parts y, split
 // into the planes at p.
@@ -230,7 +245,11 @@ void k_gemm_split(GemmArgs a) {
   using V = typename T::V;
   constexpr int KC = C::KC, MB = C::MB, NK = C::NK, NW = 4;
   constexpr bool F16 = T::F16, FWD = KIND != GK_ADJ;
+  // fp16, up to 16 rows: one wavefront stages whole rows of a chunk (forward) or whole receivers
+  // (adjoint), and so finds their scales itself
+  constexpr bool OWN = F16 && NBT == 1;
   extern __shared__ __align__(16) char s_raw[];
+  __shared__ __align__(16) float s_inv[OWN ? NP : 1][2][KC];  // OWN: the inverse scales, by slot
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1);
@@ -276,8 +295,8 @@ void k_gemm_split(GemmArgs a) {
     if (src < 0 || src >= a.ns) src = -1;
   }
   const int drow = src >= 0 ? drow_of(a, lane, src) : -1;
-  float2 sd = make_float2(1.f, 1.f);                // D's scale and its inverse (fp16)
-  if constexpr (F16) sd = pow2_scale_pair(a.dmax[k]);
+  float2 sd = make_float2(1.f, 1.f);                // D's scale and its inverse (fp16, not OWN)
+  if constexpr (F16 && !OWN) sd = pow2_scale_pair(a.dmax[k]);
 
   // D_{b,k} for the forward product: wavefront w stages rows 16 w .. 16 w + 15, a lane eight
   // receivers of one row; rows without a source and receivers past the padded row are out of
@@ -304,10 +323,21 @@ void k_gemm_split(GemmArgs a) {
         // used here and not before: hoisted above the step's products, the split would wait
         // there for these loads
         asm volatile("" : "+v"(d[q].x), "+v"(d[q].y), "+v"(d[q].z), "+v"(d[q].w));
-        x[2 * q] = d[q].x * sd.x;
-        y[2 * q] = -d[q].y * sd.x;
-        x[2 * q + 1] = d[q].z * sd.x;
-        y[2 * q + 1] = -d[q].w * sd.x;
+        x[2 * q] = d[q].x;
+        y[2 * q] = -d[q].y;
+        x[2 * q + 1] = d[q].z;
+        y[2 * q + 1] = -d[q].w;
+      }
+      float sc = sd.x;
+      if constexpr (OWN) {
+        const float2 sp = pow2_scale_pair(quad_max(amax8(x, y)));
+        sc = sp.x;
+        if ((lane & 3) == 0) s_inv[part][slot][frow] = sp.y;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        x[e] *= sc;
+        y[e] *= sc;
       }
       put_planes<PREC>(s_d + slot * C::SLOT + frow * C::FP + fg, C::FPL, x, y);
     }
@@ -337,11 +367,28 @@ void k_gemm_split(GemmArgs a) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         asm volatile("" : "+v"(d[e].x), "+v"(d[e].y));
-        x[e] = d[e].x * sd.x;
-        y[e] = d[e].y * sd.x;
+        x[e] = d[e].x;
+        y[e] = d[e].y;
+      }
+      float sc = sd.x;
+      if constexpr (OWN) {
+        const float2 sp = pow2_scale_pair(column_max(amax8(x, y)));
+        sc = sp.x;
+        if (lq == 0) s_inv[part][slot][ar] = sp.y;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        x[e] *= sc;
+        y[e] *= sc;
       }
       put_planes<PREC>(s_d + slot * C::SLOT + ar * C::AP + akk * 32 + 8 * lq, C::APL, x, y);
     }
+  };
+
+  // Inverses of D's scales for the lane's four results of a tile, rows (receivers) at + 4 lq on.
+  auto inv_scales = [&](int slot, int at) -> floatx4 {
+    if constexpr (OWN) return *reinterpret_cast<const floatx4*>(&s_inv[part][slot][at + 4 * lq]);
+    else return floatx4{sd.y, sd.y, sd.y, sd.y};
   };
 
   // Data (or the adjoint's operand) entries of the lane: batch row 16 t + 4 lq + e.
@@ -376,17 +423,19 @@ void k_gemm_split(GemmArgs a) {
       load_r(nxt, part + NP * (v + 1));  // past the last chunk: zeros
       if (active) {
         float x[8], y[8];
-        float2 sr = make_float2(1.f, 1.f);
-        if constexpr (F16) {
-          float m = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) m = fmaxf(m, fmaxf(fabsf(cur[e].x), fabsf(cur[e].y)));
-          sr = pow2_scale_pair(column_max(m));
-        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          x[e] = cur[e].x * sr.x;
-          y[e] = cur[e].y * sr.x;
+          x[e] = cur[e].x;
+          y[e] = cur[e].y;
+        }
+        float2 sr = make_float2(1.f, 1.f);
+        if constexpr (F16) {
+          sr = pow2_scale_pair(column_max(amax8(x, y)));
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            x[e] *= sr.x;
+            y[e] *= sr.x;
+          }
         }
         V brh, brl, bih, bil;
         split8<PREC>(x, brh, brl);
@@ -399,6 +448,7 @@ void k_gemm_split(GemmArgs a) {
             av[t & 1][i] = *reinterpret_cast<const V*>(p + i * C::FPL + t * 16 * C::FP);
         };
         read_a(0);
+        const floatx4 si = inv_scales(v & 1, 0);
 #pragma unroll
         for (int t = 0; t < NBT; ++t) {
           if (t + 1 < NBT) read_a(t + 1);
@@ -407,8 +457,8 @@ void k_gemm_split(GemmArgs a) {
           if constexpr (T::LO) cmma_lo<T>(av[t & 1], brh, brl, bih, bil, cr, ci, cu);
           cmma_hi<T>(av[t & 1], brh, bih, cr, ci, cu);
           if constexpr (F16) {
-            re[t] += (cr * sd.y) * sr.y;
-            im[t] += ((ci - cu) * sd.y) * sr.y;
+            re[t] += (cr * si) * sr.y;
+            im[t] += ((ci - cu) * si) * sr.y;
           } else {
             re[t] = cr;
             im[t] = ci;
@@ -505,10 +555,11 @@ void k_gemm_split(GemmArgs a) {
         for (int e = 0; e < 4; ++e) old[e] = buffer_get2(gb, goff[e]);
       }
       floatx4 gr = zero, gi = zero;
+      const floatx4 si = inv_scales(slot, m * 16);
       if (active) adjoint_tile<PREC, NBT>(p + m * 16 * C::AP + 8 * lq, srh, srl, sih, sil, gr, gi);
       if constexpr (F16) {
-        gr = (gr * sd.y) * ss.y;
-        gi = (gi * sd.y) * ss.y;
+        gr = (gr * si) * ss.y;
+        gi = (gi * si) * ss.y;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
