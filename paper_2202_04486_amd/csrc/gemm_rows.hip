@@ -145,9 +145,14 @@ struct RowsCfg {
 // pass over the spectra that this saves (64 to 88 us; forward + adjoint, us):
 //   batch  8: 45 + 70, 49 + 70 -> 64, 53      batch 32: 67 + 80, 68 + 80 -> 87, 118
 //   batch 16: 46 + 70, 49 + 70 -> 69, 72      batch 64: 110 + 88 -> 140 (forward)
-template <int PREC, int NBT, int KIND, bool ACC, bool REC, bool RES, int NW>
-__global__ __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(NBT >= 3 || (REC && NBT == 2 && KIND == GK_FWD) ? 2 : NBT == 2 || (REC && !RES) ? 3 : REC ? 4 : 5)))
+//
+// NP = 4 (up to 16 batch rows, few column blocks): the four wavefronts of a workgroup share one
+// block.  Wavefront p takes the receiver chunks p, p + 4, ... of both products, staged by
+// itself in LDS slots of its own; in between the four add their sums through LDS, so that each
+// holds the residual.
+template <int PREC, int NBT, int KIND, bool ACC, bool REC, bool RES, int NW, int NP>
+__global__ __launch_bounds__(64 * NW * NP)
+__attribute__((amdgpu_waves_per_eu(NP > 1 ? (KIND == GK_FUSED && !RES ? 3 : 4) : NBT >= 3 || (REC && NBT == 2 && KIND == GK_FWD) ? 2 : NBT == 2 || (REC && !RES) ? 3 : REC ? 4 : 5)))
 void k_gemm_rows(GemmArgs a, int nslot) {
   using C = RowsCfg<NBT>;
   using E = std::conditional_t<C::WIDE, Left, float2>;
@@ -158,11 +163,13 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   constexpr bool RFWD = REC && KIND == GK_FWD, RADJ = REC && KIND == GK_ADJ;
   constexpr int HALF = RADJ ? MB / 2 : MB;        // rows of D; the others are conj(V)'s
   static_assert(!REC || (PREC == MDD_PREC_FP32 && KIND != GK_FUSED), "reciprocity");
+  static_assert(NP == 1 || (NW == 1 && !REC), "a wavefront without a block would miss a barrier");
   extern __shared__ __align__(16) char s_raw[];
-  E* const s_d = reinterpret_cast<E*>(s_raw);     // nslot chunks of D [row][receiver]
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = NP == 1 ? wid : 0, part = NP == 1 ? 0 : wid;
+  const int tid = threadIdx.x - 64 * part, lane = tid & 63;
+  E* const s_d = reinterpret_cast<E*>(s_raw) + part * nslot * SLOT;  // nslot chunks of D [row][receiver]
   const int lr = lane & 15, lq = lane >> 4;
   // the column groups of one frequency share an XCD, whose L2 then serves D_k once; the
   // blocks of a frequency are spread evenly over its groups
@@ -176,7 +183,9 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   const int blk = active ? blk0 + wave : blk0;
   const long long rowstride = (long long)a.nvb * a.nf * CB;
   const unsigned rs32 = (unsigned)rowstride;
-  const int nr = a.nr, nc = (nr + KC - 1) / KC;
+  // this wavefront's chunks c = 0 .. nc - 1 are the receivers' chunks NP c + part
+  const int nr = a.nr, nc = (nr + NP * KC - 1) / (NP * KC);
+  auto chunk = [&](int c) { return NP * c + part; };
 
   // R_k rows of a chunk -> registers (the right operand's layout: k-step q, lane quarter
   // lq is receiver rstep(q) + RQ lq of the chunk); rows at or past nr are out of bounds: zeros.
@@ -193,7 +202,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
     return buffer_at(base + r0 * rowstride + col, n ? (unsigned)n * rs32 * 8u - (unsigned)col * 8u : 0u);
   };
   auto load_r = [&](float2 (&dst)[KS], int c) {
-    const auto rb = rows_at(a.F, c * KC, KC);
+    const auto rb = rows_at(a.F, chunk(c) * KC, KC);
 #pragma unroll
     for (int q = 0; q < KS; ++q) dst[q] = buffer_get2(rb, roff[q]);
   };
@@ -254,7 +263,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   // padded row are out of bounds: zeros.
   const char* dbase = reinterpret_cast<const char*>(a.Df + (long long)k * a.dns * a.nrp);
   const unsigned dbytes = (unsigned)a.dns * (unsigned)a.nrp * 8u;
-  static_assert(NTH / (KC / 2) == 16, "of_v");    // a thread's rows are 16 apart,
+  static_assert(!RADJ || NTH / (KC / 2) == 16, "of_v");  // a thread's rows are 16 apart,
   auto of_v = [&](int q) { return RADJ && 16 * q + 4 * wave >= HALF; };  // a wavefront's four
   unsigned doff[FPT];
 #pragma unroll
@@ -268,9 +277,10 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       doff[q] = ((unsigned)row * (unsigned)a.nrp + rr) * 8u;
     if (row < 0) doff[q] = PAST_END;
   }
-  constexpr int DB = RES ? 8 : 1;                 // chunks of D requested at once
+  constexpr int DB = RES ? 8 / NP : 1;            // chunks of D requested at once
   float4 dv[DB][FPT];
-  auto load_d = [&](int c, float4 (&d)[FPT]) {
+  auto load_d = [&](int own, float4 (&d)[FPT]) {
+    const int c = chunk(own);
     const auto db = buffer_at(dbase + (long long)c * KC * 8, dbytes - (unsigned)(c * KC) * 8u);
     const auto vb = buffer_at(a.Bsp + (long long)c * (KC / CB) * a.nf * CB,
                               RADJ ? (unsigned)(a.nb * a.nvb - c * (KC / CB)) * (unsigned)a.nf * (CB * 8u) : 0u);
@@ -428,6 +438,24 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       im[t] += acc[t].t3;
     }
     if constexpr (KIND == GK_FUSED && NBT >= 3) load_u();
+    if constexpr (NP > 1) {                       // the parts' sums, added in order
+      __shared__ float2 s_sum[NP][MB][16];
+#pragma unroll
+      for (int t = 0; t < NBT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_sum[part][t * 16 + lq * 4 + e][lr] = make_float2(re[t][e], im[t][e]);
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NBT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float2 z = s_sum[0][t * 16 + lq * 4 + e][lr];
+#pragma unroll
+          for (int p = 1; p < NP; ++p) z = cadd(z, s_sum[p][t * 16 + lq * 4 + e][lr]);
+          re[t][e] = z.x;
+          im[t][e] = z.y;
+        }
+    }
   }
 
   // residual and float64 loss partial (or predicted data, or the adjoint's operand)
@@ -443,14 +471,14 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       if constexpr (KIND == GK_FUSED) lpart += (double)z.x * z.x + (double)z.y * z.y;
       if constexpr (KIND == GK_FWD) {
         if constexpr (REC) z = cscale(z, 0.5f);
-        if (row < a.nb) a.Bsp[(((size_t)row * a.nvb + blk) * a.nf + k) * CB + lr] = z;
+        if (row < a.nb && part == 0) a.Bsp[(((size_t)row * a.nvb + blk) * a.nf + k) * CB + lr] = z;
       }
       re[t][e] = z.x;
       im[t][e] = z.y;
     }
   if constexpr (KIND == GK_FUSED) {
     lpart = wave_sum(lpart);
-    if (lane == 0) a.loss_part[k * a.nvb + blk] = lpart * (k == 0 || 2 * k == a.nt ? 1.0 : 2.0);
+    if (lane == 0 && part == 0) a.loss_part[k * a.nvb + blk] = lpart * (k == 0 || 2 * k == a.nt ? 1.0 : 2.0);
   }
   if constexpr (KIND == GK_FWD) return;
 
@@ -474,7 +502,7 @@ void k_gemm_rows(GemmArgs a, int nslot) {
     read_a(0);
 #pragma unroll
     for (int m = 0; m < KC / 16; ++m) {
-      const int r0 = c * KC + m * 16;
+      const int r0 = chunk(c) * KC + m * 16;
       const auto gb = rows_at(gbase, r0, 16);
       float2 old[4];
       if constexpr (ACC) {
@@ -515,11 +543,11 @@ void k_gemm_rows(GemmArgs a, int nslot) {
   for (int v = nc + 1; v < 2 * nc; ++v) visit(v, std::false_type{});
 }
 
-template <int PREC, int NBT, bool RES, int NW>
+template <int PREC, int NBT, bool RES, int NW, int NP = 1>
 hipError_t launch_nw(int kind, const GemmArgs& a, int nslot, hipStream_t s) {
-  const size_t sm = (size_t)RowsCfg<NBT>::ESZ * RowsCfg<NBT>::SLOT * nslot;
+  const size_t sm = (size_t)RowsCfg<NBT>::ESZ * RowsCfg<NBT>::SLOT * nslot * NP;
   const int ncg = (a.nvb + NW - 1) / NW;
-  const dim3 grid(a.nf * ncg), block(64 * NW);
+  const dim3 grid(a.nf * ncg), block(64 * NW * NP);
   auto go = [&](auto kernel) {
     if (sm > 65536)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -527,23 +555,37 @@ hipError_t launch_nw(int kind, const GemmArgs& a, int nslot, hipStream_t s) {
     hipLaunchKernelGGL(kernel, grid, block, sm, s, a, nslot);
     return hipGetLastError();
   };
-  constexpr bool R3 = PREC == MDD_PREC_FP32;      // reciprocity: the three-product form only
+  constexpr bool R3 = PREC == MDD_PREC_FP32 && NP == 1;  // reciprocity: the three-product form only
   switch (kind) {
     case GK_FUSED:
-      return a.gacc ? go(k_gemm_rows<PREC, NBT, GK_FUSED, true, false, RES, NW>)
-                    : go(k_gemm_rows<PREC, NBT, GK_FUSED, false, false, RES, NW>);
+      return a.gacc ? go(k_gemm_rows<PREC, NBT, GK_FUSED, true, false, RES, NW, NP>)
+                    : go(k_gemm_rows<PREC, NBT, GK_FUSED, false, false, RES, NW, NP>);
     case GK_FWD:
       if constexpr (R3) {
-        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_FWD, false, true, RES, NW>);
+        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_FWD, false, true, RES, NW, NP>);
       }
-      return go(k_gemm_rows<PREC, NBT, GK_FWD, false, false, RES, NW>);
+      return go(k_gemm_rows<PREC, NBT, GK_FWD, false, false, RES, NW, NP>);
     case GK_ADJ:
       if constexpr (R3) {
-        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, true, RES, NW>);
+        if (a.rec) return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, true, RES, NW, NP>);
       }
-      return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, false, RES, NW>);
+      return go(k_gemm_rows<PREC, NBT, GK_ADJ, false, false, RES, NW, NP>);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Up to 16 rows: four wavefronts on one block where a wavefront per block would leave the chip
+// idle behind its chain of chunks, up to four workgroups a CU (fused, us; a wavefront per block ->
+// four, in brackets the kernel before both):
+//   receivers  blocks:  60                 200                771                1285
+//      64               8.5 ->  7.8 (10)   8.6 ->  8.0 (8)    12 -> 13 (13)      16 -> 18 (17)
+//     200               15 ->  9.1 (15)    17 ->  11 (12)     24 -> 20 (21)      25 -> 26 (26)
+//     400               26 ->  15 (19)     29 ->  17 (23)     37 -> 31 (34)      39 -> 43 (53)
+//    1000               58 ->  24 (44)     57 ->  24 (50)     78 -> 53 (73)      92 -> 90 (133)
+// Few receivers leave wavefronts without a chunk: there only up to a workgroup a CU, and not
+// with a single chunk (a step of 32 traces 12.9 -> 13.3 us).
+inline bool share_block(const GemmArgs& a) {
+  return a.nr > 32 && a.nf * a.nvb <= (a.nr > 128 ? 1024 : 256);
 }
 
 // LDS slots: the adjoint finds the last nslot chunks of D in LDS and fetches the others
@@ -556,6 +598,10 @@ hipError_t launch_nbt(int kind, const GemmArgs& a, hipStream_t s) {
   using C = RowsCfg<NBT>;
   const int nc = (a.nr + C::KC - 1) / C::KC, slot = C::ESZ * C::SLOT;
   if constexpr (NBT == 1) {
+    if (!a.rec && share_block(a)) {
+      const int np = (nc + 3) / 4;                // chunks per wavefront
+      return np <= 3 ? launch_nw<PREC, NBT, true, 1, 4>(kind, a, np, s) : launch_nw<PREC, NBT, false, 1, 4>(kind, a, 2, s);
+    }
     if (nc * slot <= 45000) return launch_nw<PREC, NBT, true, 4>(kind, a, nc, s);
   }
   const int most = (NBT == 1 ? 32768 : NBT == 2 ? 52300 : 70000) / slot;
