@@ -132,6 +132,17 @@ struct RowsCfg {
   }
 };
 
+// Wavefronts per SIMD that the registers are cut for.  At up to 16 rows five where D is resident
+// (the three-product fused form spills one register so: 230 to 260 receivers 1 % faster than
+// with four, 300 the same) and four where its chunks come in turn (with five 9 registers were
+// spilled: 700 receivers, 2600 blocks 134 us with five, 116 with four).
+constexpr int waves_per_simd(int nbt, int kind, bool rec, bool res, int np) {
+  if (np > 1) return kind == GK_FUSED && !res ? 3 : 4;
+  if (nbt > 1) return nbt >= 3 || (rec && kind == GK_FWD) ? 2 : 3;
+  if (rec) return res ? 4 : 3;
+  return res ? 5 : 4;
+}
+
 // ACC: the adjoint product is added to what Gout holds (a sum over batches).
 //
 // REC: with the reciprocity average C_r (nr = nvs) folded in, forward and adjoint kinds.
@@ -152,7 +163,7 @@ struct RowsCfg {
 // holds the residual.
 template <int PREC, int NBT, int KIND, bool ACC, bool REC, bool RES, int NW, int NP>
 __global__ __launch_bounds__(64 * NW * NP)
-__attribute__((amdgpu_waves_per_eu(NP > 1 ? (KIND == GK_FUSED && !RES ? 3 : 4) : NBT >= 3 || (REC && NBT == 2 && KIND == GK_FWD) ? 2 : NBT == 2 || (REC && !RES) ? 3 : REC ? 4 : 5)))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd(NBT, KIND, REC, RES, NP))))
 void k_gemm_rows(GemmArgs a, int nslot) {
   using C = RowsCfg<NBT>;
   using E = std::conditional_t<C::WIDE, Left, float2>;
