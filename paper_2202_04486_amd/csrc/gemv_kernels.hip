@@ -162,9 +162,11 @@ __global__ __launch_bounds__(GV_THREADS) void k_gemv_wide(GemmArgs a) {
     }
     if constexpr (KIND != GK_FWD) {
 #pragma unroll
-      for (int r = 0; r < GV_GR; ++r)
+      for (int r = 0; r < GV_GR; ++r) {
+        if (src[r] < 0) continue;  // its loads read a row that is not its own
 #pragma unroll
         for (int m = 0; m < MQ; ++m) cmac_conj(gv[m], dv[r][m], res[r]);
+      }
     }
   }
 
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(GV_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
       if constexpr (KIND == GK_FUSED) lpart += (double)z[b].x * z[b].x + (double)z[b].y * z[b].y;
       if constexpr (KIND == GK_FWD) {
         if (lane == 0 && i + b < i1) a.Bsp[spec2(i + b)] = z[b];
-      } else {
+      } else if (ok) {  // (the loads of a rejected or missing row read another one)
 #pragma unroll
         for (int m = 0; m < MQ; ++m) cmac_conj(gv[m], d[b][m], z[b]);
       }
