@@ -9,10 +9,11 @@
 //
 // One pass over D_b: each row of D_{b,k} is loaded once into registers, reduced to
 // res_i and, still in registers, multiplied into the adjoint sum.  k_gemv gives each row to
-// one wavefront; k_gemv_wide, for more than 1664 receivers, to the workgroup.  The rows of
-// one frequency are split into P groups (one workgroup each) so that the grid covers the
-// chip; with P > 1 the group partials of g_k go to a scratch buffer and are added in group
-// order by the trace kernel that transforms them, or (the full gradient) by k_gemv_sum.
+// one wavefront; k_gemv_wide, for more than 1664 receivers and where rows are few, to the
+// workgroup.  The rows of one frequency are split into P groups (one workgroup each) so that
+// the grid covers the chip; with P > 1 the group partials of g_k go to a scratch buffer and
+// are added in group order by the trace kernel that transforms them, or (the full gradient)
+// by k_gemv_sum.
 //
 // Layout at nvs = 1 (the trace kernels see one row of nr columns): model and gradient
 // spectra hold receiver j at frequency k at ((j / 16) * nf + k) * 16 + j % 16; batch
@@ -392,13 +393,42 @@ __global__ __launch_bounds__(GV_THREADS) void k_gemv_sum(GemmArgs a) {
   store_pair(a, k, q, s);
 }
 
+// Row groups per frequency, at least 8 rows each.  One wavefront per row: about one
+// workgroup per CU, since every group's partial of g_k is written and read once more (3D
+// patch with one virtual source, products + update: 49.5 us with 2 groups, 56 with 3, 60
+// with 4).  The wide kernel waits at a barrier per two rows and wants about three
+// workgroups per CU, and at least four groups.
+int row_groups(int nb, int nf, bool wide) {
+  const int most = (nb + 7) / 8;
+  int want = ((wide ? 3 : 1) * 256 + nf - 1) / nf;
+  if (wide && want < 4) want = 4;
+  return want < most ? want : most;
+}
+
+// A workgroup per row beats a wavefront per row (us, a wavefront -> a workgroup)
+//   where most wavefronts would have no row: 1664 receivers, 257 bins, 2 rows fused 10.2 ->
+//     7.4, 600 receivers 8.3 -> 6.2, but 8 rows 13.4 -> 14.2; adjoint alone, with no dot product
+//     to wait for, 8 rows 10.3 -> 8.3;
+//   where the registers of the long rows allow two workgroups a CU and there are more than
+//     that: 513 bins, 8 rows 22.4 -> 17.0;
+//   in the forward kind with long rows: 257 bins, 64 rows 40 -> 35 (8 rows 9.4 -> 10.9).
+// The forward kind leaves no partials: with many rows at least two groups (1100 receivers, 257
+// bins, 64 rows 28.8 -> 26.7).
 template <int KIND>
-hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
+hipError_t launch_rows(GemmArgs a, hipStream_t s) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(a.nf * a.P), dim3(GV_THREADS), 0, s, a);
     return hipGetLastError();
   };
   const int mq = (a.nrp / 2 + 63) / 64;            // receiver pairs per lane
+  const bool long_forward = KIND == GK_FWD && mq > 10 && a.nf > 256 && a.nb > 8;
+  if (long_forward) a.P = row_groups(a.nb, a.nf, true);
+  else if (KIND == GK_FWD && a.nb >= 32 && a.P < 2) a.P = 2;
+  if (mq > GV_MQ || long_forward || (mq > 4 && a.nb <= 4) || (mq > 8 && a.nb <= 8 && (KIND == GK_ADJ || a.nf > 512))) {
+    if (mq <= 8) return go(k_gemv_wide<KIND, 2>);
+    if (mq <= 16) return go(k_gemv_wide<KIND, 4>);
+    return go(k_gemv_wide<KIND, 8>);
+  }
   if (mq <= 1) return go(k_gemv<KIND, 1, 4>);
   if (mq <= 2) return go(k_gemv<KIND, 2, 4>);
   if (mq <= 3) return go(k_gemv<KIND, 3, 2>);
@@ -406,9 +436,7 @@ hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
   if (mq <= 6) return go(k_gemv<KIND, 6, 2>);
   if (mq <= 8) return go(k_gemv<KIND, 8, 1>);
   if (mq <= 10) return go(k_gemv<KIND, 10, 1>);
-  if (mq <= 13) return go(k_gemv<KIND, 13, 1>);
-  if (mq <= 16) return go(k_gemv_wide<KIND, 4>);   // (16 pairs a lane: 76 registers spilled)
-  return go(k_gemv_wide<KIND, 8>);
+  return go(k_gemv<KIND, 13, 1>);                  // (16 pairs a lane: 76 registers spilled)
 }
 
 template <int KIND>
@@ -422,18 +450,7 @@ hipError_t launch_kind(const GemmArgs& a, bool sum, hipStream_t s) {
 
 }  // namespace
 
-// Row groups per frequency, at least 8 rows each.  One wavefront per row: about one
-// workgroup per CU, since every group's partial of g_k is written and read once more (3D
-// patch with one virtual source, products + update: 49.5 us with 2 groups, 56 with 3, 60
-// with 4).  The wide kernel waits at a barrier per two rows and wants about three
-// workgroups per CU, and at least four groups.
-int gemv_groups(int nb, int nf, int nr) {
-  const int most = (nb + 7) / 8;
-  const bool wide = round16(nr) / 2 > 64 * GV_MQ;
-  int want = ((wide ? 3 : 1) * 256 + nf - 1) / nf;
-  if (wide && want < 4) want = 4;
-  return want < most ? want : most;
-}
+int gemv_groups(int nb, int nf, int nr) { return row_groups(nb, nf, round16(nr) / 2 > 64 * GV_MQ); }
 
 hipError_t launch_gemv(int kind, const GemmArgs& a, bool sum, hipStream_t s) {
   if (a.nb < 1 || a.nb > NB_LIMIT || a.nvs != 1 || a.P < 1) return hipErrorInvalidValue;

@@ -31,6 +31,21 @@ def test_every_width(nr, nb):
     assert abs(gn.item() - np.sum(go ** 2)) <= 2 * TOL * np.sum(go ** 2)
 
 
+@pytest.mark.parametrize("nr,nb", [(1025, 8), (1025, 9), (1281, 8), (1600, 6), (300, 5)])
+def test_many_bins(nr, nb):
+    """More frequencies than workgroups that the long rows' registers allow at once."""
+    ns, nt, nf = 10, 1024, 513
+    d, u, r = random_case(ns, nr, 1, nt, seed=nr)
+    plan = make_plan(d, u, nb_max=nb, nf=nf)
+    idx = np.random.default_rng(nb).integers(0, ns, size=nb).astype(np.int32)
+    it = T(idx, torch.int32)
+    assert relerr(H(plan.mdc_forward(T(r), it)), freq.mdc(d[idx], r, nf)) <= TOL
+    G, loss, _ = plan.mdd_stoch_grad(T(r), it)
+    lo, go = freq.batch_loss_grad(d, r, u, idx, nf)
+    assert relerr(H(G), go) <= TOL
+    assert abs(loss.item() - lo) <= TOL * lo
+
+
 @pytest.mark.parametrize("nb", [3, 20, 40])
 @pytest.mark.parametrize("nr", [35, 129, 300, 400, 600, 900, 1100, 1600, 1700, 4000])
 def test_rejected_entries_read_no_source(nr, nb):
