@@ -268,7 +268,7 @@ struct mdd_plan {
                                double* gnorm2_out) {
     ReduceArgs r{};
     r.loss_part = lossp();
-    r.n_loss = n_loss(nb);
+    r.n_loss = loss_out ? n_loss(nb) : 0;
     r.loss_scale = 1.0 / (2.0 * d.nt);
     r.oob = oob();
     r.idx = idx;
@@ -276,12 +276,12 @@ struct mdd_plan {
     r.ns = d.ns;
     r.oob_pos = streamed_data() ? 1 : 0;
     r.gn_part = gnp();
-    r.n_gn = n_gn();
+    r.n_gn = gnorm2_out ? n_gn() : 0;
     r.loss_out = loss_out;
     r.gnorm2_out = gnorm2_out;
     r.stage = red2();
     a.part = gnp();
-    const bool wanted = loss_out || gnorm2_out, here = wanted && r.n_gn <= RED_IN_UPDATE;
+    const bool wanted = loss_out || gnorm2_out, here = wanted && n_gn() <= RED_IN_UPDATE;
     if (here) {
       a.red = r;
       a.done = reinterpret_cast<unsigned*>(tw() + 2 * d.nt - 1);  // past the twiddle tables
@@ -323,7 +323,7 @@ struct mdd_plan {
     r.nb = 0;
     r.ns = d.ns;
     r.gn_part = gnp();
-    r.n_gn = n_gn();
+    r.n_gn = gnorm2_out ? n_gn() : 0;
     r.loss_out = loss_out;
     r.gnorm2_out = gnorm2_out;
     r.stage = red2();
