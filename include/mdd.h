@@ -209,7 +209,8 @@ mdd_status mdd_stoch_grad(mdd_plan* plan, const float* R, const int32_t* idx, in
  * in time on one GPU (other streams, other threads) race and must be serialised by
  * the caller; a call's results do not depend on what an earlier call left there.
  * Errors: EINVAL (NULL, flags, a stream of another device), ESHAPE, EUNSUPPORTED,
- * ELIMIT (mdd_workspace_bytes(dims) above MDD_NOALLOC_WORKSPACE_BYTES), EHIP. */
+ * ELIMIT (mdd_workspace_bytes(dims) without MDD_FLAG_STORE_RF, which has no effect here,
+ * above MDD_NOALLOC_WORKSPACE_BYTES), EHIP. */
 #define MDD_NOALLOC_WORKSPACE_BYTES (64u << 20)
 mdd_status mdd_stoch_grad_noalloc(const mdd_dims* dims, const float* d, const float* u,
                                   const int32_t* onset, const float* R, const int32_t* idx,

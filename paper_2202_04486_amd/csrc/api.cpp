@@ -29,7 +29,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 bool valid_nt(int nt) { return nt == 128 || nt == 256 || nt == 512 || nt == 1024; }
 
 struct Layout {
-  size_t tw, df, uf, oob, oobp, onset, f, bsp, lossp, gnp, dmx, red2, f2, sidx, gvp, total;
+  size_t tw, df, uf, oob, oobp, onset, f, bsp, lossp, gnp, dmx, red2, f2, sidx, gvp, sig, total;
 };
 
 // Sources per batch of the full gradient, whatever nb_max: the largest batch the products
@@ -78,6 +78,10 @@ Layout make_layout(const mdd_dims& d) {
   L.f2 = take(full ? c8 * d.nr * nvb * d.nf * CB : 0);
   L.sidx = take(full ? sizeof(int32_t) * d.ns : 0);
   L.gvp = take(ngv > 1 ? sizeof(float4) * d.nf * ngv * (nrp / 2) : 0);  // row-group partials
+  // Partial sums of the power iteration: the model spectra's buffer, or the full gradient's
+  // second one, except where the first may hold spectra that a later step starts from.
+  const bool own = (d.flags & MDD_FLAG_STORE_RF) && !full && !(d.flags & MDD_FLAG_STREAM_KERNEL);
+  L.sig = take(own ? sigma_scratch_bytes(d.nf, d.nr, sigma_groups(d.nf, d.ns, d.nr, nvb)) : 0);
   L.total = o;
   return L;
 }
@@ -140,6 +144,10 @@ struct mdd_plan {
   double* red2() const { return at<double>(L.red2); }
   int32_t* sidx() const { return at<int32_t>(L.sidx); }
   float4* gvp() const { return at<float4>(L.gvp); }
+  void* sigma_scratch() const {
+    if (full()) return F2();  // between two calls nothing lives there
+    return (d.flags & MDD_FLAG_STORE_RF) ? at<void>(L.sig) : F();
+  }
   bool full() const { return (d.flags & MDD_FLAG_FULL_GRAD) != 0; }
   // MDD_FLAG_STREAM_KERNEL: Df holds the rows of the last staged batch (staged_nb rows).
   bool streamed() const { return (d.flags & MDD_FLAG_STREAM_KERNEL) != 0; }
@@ -654,7 +662,9 @@ mdd_status mdd_stoch_grad_noalloc(const mdd_dims* dims, const float* d, const fl
   MDD_TRY(check_dims(dims));
   if (dims->flags & (MDD_FLAG_STREAM_KERNEL | MDD_FLAG_FULL_GRAD)) return MDD_EINVAL;
   if (nb < 1 || nb > dims->nb_max) return MDD_ESHAPE;
-  const Layout L = make_layout(*dims);
+  mdd_dims d1 = *dims;
+  d1.flags &= ~MDD_FLAG_STORE_RF;  // one gradient: nothing is stored for a next call
+  const Layout L = make_layout(d1);
   if (L.total > static_workspace_bytes()) return MDD_ELIMIT;
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   int dev = -1;
@@ -667,7 +677,7 @@ mdd_status mdd_stoch_grad_noalloc(const mdd_dims* dims, const float* d, const fl
   void* ws = nullptr;
   if (static_workspace(dev, &ws) != hipSuccess) return MDD_EHIP;
   mdd_plan p;  // host object on the stack; its event lists stay empty
-  if (init_plan(&p, dims, L, ws, stream) != hipSuccess) return MDD_EHIP;
+  if (init_plan(&p, &d1, L, ws, stream) != hipSuccess) return MDD_EHIP;
   MDD_TRY(mdd_set_kernel(&p, d));
   MDD_TRY(mdd_set_data(&p, u));
   MDD_TRY(mdd_set_mask(&p, onset));
@@ -784,10 +794,10 @@ mdd_status mdd_sigma_max2(mdd_plan* p, int32_t iters, double* lam_out) {
   if (!p || !lam_out) return MDD_EINVAL;
   if (iters < 1) return MDD_EINVAL;
   if (!p->kernel_set || p->streamed()) return MDD_ESTATE;  // needs every source's D_k
-  p->spec_model = nullptr;  // the model spectra's buffer holds the iteration's partial sums
   return p->run(MDD_KC_REDUCE, [&] {
     return launch_sigma(p->Df(), p->d.nf, p->d.ns, p->d.nr, p->nrp, iters,
-                        sigma_groups(p->d.nf, p->d.ns, p->d.nr, p->nvb), p->F(), lam_out, p->stream);
+                        sigma_groups(p->d.nf, p->d.ns, p->d.nr, p->nvb), p->sigma_scratch(), lam_out,
+                        p->stream);
   });
 }
 

@@ -142,6 +142,7 @@ hipError_t launch_freq_absmax(const float2* Df, int nf, long long count, long lo
 // of group partials [nf][P][nr] complex float64 and [nf][P] float64.  sigma_groups keeps
 // that within 128 nr nvb nf bytes, the model spectra's size.
 int sigma_groups(int nf, int ns, int nr, int nvb);
+inline size_t sigma_scratch_bytes(int nf, int nr, int P) { return (size_t)nf * P * (32 * (size_t)nr + 8); }
 hipError_t launch_sigma(const float2* Df, int nf, int ns, int nr, int nrp, int iters, int P,
                         void* scratch, double* lam_out, hipStream_t s);
 
