@@ -76,7 +76,7 @@ struct TraceArgs {
 };
 
 // Workgroups (gradient-norm partials) up to which the update kernel does the reduction: one
-// workgroup a CU, where it replaces a launch (a 32-trace step 15.8 -> 13.3 us).  With more,
+// workgroup a CU, where it replaces a launch (a 32-trace step 15.8 -> 13.1 us).  With more,
 // each of them still waits for its partial and its count to arrive, one round after the
 // other: 2200 workgroups 50.6 -> 63.6 us a step, 5200 in the gradient kernel 196 -> 213 us.
 constexpr int RED_IN_UPDATE = 256;

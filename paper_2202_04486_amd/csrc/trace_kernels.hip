@@ -255,23 +255,11 @@ __device__ __forceinline__ void loss_here(const ReduceArgs& r, double* red) {
   if (tid == 0 && r.loss_out) r.loss_out[0] = l * r.loss_scale + o;
 }
 
-// ||g||^2, by the launch's last workgroup: the partials were stored past the L2 caches (agent
-// scope) by workgroups on other XCDs and are read the same way.
+// ||g||^2, by the launch's last workgroup, which has acquired the others' partials.
 template <int NTH>
 __device__ __forceinline__ void norm_here(const ReduceArgs& r, const double* part, double* red) {
   double g = 0.0;
-  int i = threadIdx.x;
-  auto at = [&](int j) {
-    return __hip_atomic_load(part + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  for (; i + 7 * NTH < r.n_gn; i += 8 * NTH) {
-    double x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = at(i + j * NTH);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) g += x[j];
-  }
-  for (; i < r.n_gn; i += NTH) g += at(i);
+  for (int i = threadIdx.x; i < r.n_gn; i += NTH) g += part[i];
   g = tile_sum<NTH / 64>(g, red);
   if (threadIdx.x == 0 && r.gnorm2_out) r.gnorm2_out[0] = g;
 }
@@ -533,12 +521,13 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
     const double tot = tile_sum<NW>(part, s_red);
     if (tid == 0) {
       if (C::UPD && a.done) {
-        // The partial has to be in memory before the count says so.  The store and the count
-        // are agent-scope accesses, which go past the XCD's L2, and the wait orders them: a
-        // release fence would write back the whole L2 (the update kernel took 1.05 ms so).
+        // The partial is in memory before the count says so, and the workgroup that finds every
+        // other one counted reads the partials after that (release and acquire).  The release
+        // writes the XCD's L2 back, which a few workgroups can afford (patch with one virtual
+        // source, 200 of them: 1.0 us a step; 2.5 us for a launch of its own instead).  The
+        // partial itself goes past the L2 at once, 0.3 us less to wait for.
         __hip_atomic_store(a.part + bid, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+        s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
                  gridDim.x - 2;
       } else {
         a.part[bid] = tot;
