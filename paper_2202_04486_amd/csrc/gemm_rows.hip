@@ -102,9 +102,14 @@ __device__ __forceinline__ void fold(Tile& t, floatx4& re, floatx4& im) {
     const float xr = PREC == MDD_PREC_FP32 ? t.t1[i] - t.t2[i] : t.t2[i];
     const float xi = PREC == MDD_PREC_FP32 ? t.t1[i] + t.t3[i] : t.t3[i];
     const float sr = re[i] + xr, si = im[i] + xi;
-    if constexpr (PREC == MDD_PREC_FP32) t.t2[i] = (sr - re[i]) - xr;  // subtracted
-    else t.t2[i] = xr - (sr - re[i]);
-    t.t3[i] = xi - (si - im[i]);
+    const float er = xr - (sr - re[i]), ei = xi - (si - im[i]);
+    if constexpr (PREC == MDD_PREC_FP32) {
+      t.t2[i] = -er;                              // subtracted
+      t.t3[i] = ei;
+    } else {                                      // an infinite sum has no error (inf - inf)
+      t.t2[i] = er == er ? er : 0.f;
+      t.t3[i] = ei == ei ? ei : 0.f;
+    }
     re[i] = sr;
     im[i] = si;
   }
