@@ -52,7 +52,7 @@ Layout make_layout(const mdd_dims& d) {
     o += align256(bytes);
     return at;
   };
-  L.tw = take(c8 * 2 * d.nt);  // twiddle tables (at most 2 nt entries)
+  L.tw = take(c8 * 2 * d.nt);  // twiddle tables, slots and count of the update's reduction
   // kernel spectra: every source, or (MDD_FLAG_STREAM_KERNEL) the staged batch rows
   const size_t drows = (d.flags & MDD_FLAG_STREAM_KERNEL) ? d.nb_max : d.ns;
   L.df = take(c8 * d.nf * drows * nrp);
@@ -289,10 +289,11 @@ struct mdd_plan {
     r.gnorm2_out = gnorm2_out;
     r.stage = red2();
     a.part = gnp();
-    const bool wanted = loss_out || gnorm2_out, here = wanted && n_gn() <= RED_IN_UPDATE;
-    if (here) {
+    const bool wanted = loss_out || gnorm2_out, here = wanted && n_gn() <= red_in_update(d.nt);
+    if (here) {  // the slots and the count are past the twiddle tables
       a.red = r;
-      a.done = reinterpret_cast<unsigned*>(tw() + 2 * d.nt - 1);  // past the twiddle tables
+      a.done = reinterpret_cast<unsigned*>(tw() + 2 * d.nt - 1);
+      a.part = reinterpret_cast<double*>(tw() + 2 * d.nt - 1 - red_in_update(d.nt));
     }
     MDD_TRY(run(MDD_KC_UPDATE, [&] { return launch_trace(mode, a, stream); }));
     if (!wanted || here) return MDD_OK;

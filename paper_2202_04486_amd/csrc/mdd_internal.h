@@ -70,16 +70,19 @@ struct TraceArgs {
   int P, npair;
   // Gradient / update modes: the launch does the reduction `red` as well (gn_part is `part`):
   // a workgroup of its own the loss, the last of the others ||g||^2.  `done` counts them, 0
-  // before and after.  NULL: the reduction is another launch.
+  // before and after, and `part` holds no partial before and after.  NULL: the reduction is
+  // another launch.
   unsigned* done;
   ReduceArgs red;
 };
 
 // Workgroups (gradient-norm partials) up to which the update kernel does the reduction: one
-// workgroup a CU, where it replaces a launch (a 32-trace step 15.8 -> 13.1 us).  With more,
+// workgroup a CU with the loss's own, where it replaces a launch (a 32-trace step 15.8 -> 12.8
+// us; 192 workgroups 20.3 -> 19.3 us a gradient, 256 and the loss's 20.7 -> 21.4).  With more,
 // each of them still waits for its partial and its count to arrive, one round after the
 // other: 2200 workgroups 50.6 -> 63.6 us a step, 5200 in the gradient kernel 196 -> 213 us.
-constexpr int RED_IN_UPDATE = 256;
+// At nt = 128 half of that, what the 2 nt entries have room for past the twiddle tables.
+__host__ __device__ constexpr int red_in_update(int nt) { return nt == 128 ? 128 : 255; }
 
 enum GemmKind : int {
   GK_FUSED = 0,   // Res = D_b R_k - U_b (loss partials); G_k = D_b^H Res, written over R_k

@@ -240,6 +240,13 @@ __device__ __forceinline__ double tile_sum(double v, double* red) {
   return s;
 }
 
+// What a slot holds before its partial is stored: a NaN that no sum can give (a NaN among
+// float64 sums of float32 values has zeros in its last 29 bits).
+constexpr long long NO_PARTIAL = 0x7ff8000000000001LL;
+__device__ __forceinline__ double partial_at(const double* slot) {
+  return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The loss (see k_reduce for the sum), by a workgroup of its own beside the update's: the
 // partials are an earlier launch's.
 template <int NTH>
@@ -255,13 +262,21 @@ __device__ __forceinline__ void loss_here(const ReduceArgs& r, double* red) {
   if (tid == 0 && r.loss_out) r.loss_out[0] = l * r.loss_scale + o;
 }
 
-// ||g||^2, by the launch's last workgroup, which has acquired the others' partials.
+// ||g||^2, by the launch's last workgroup, over the others' slots.  The count says that every
+// partial has been stored, not that it is visible here: no fence orders the two (a release
+// writes the whole L2 back; 200 workgroups took 1 us longer with it).  So a slot is read until
+// it holds something else than NO_PARTIAL, which it is given back for the next launch.
 template <int NTH>
-__device__ __forceinline__ void norm_here(const ReduceArgs& r, const double* part, double* red) {
+__device__ __forceinline__ void norm_here(const ReduceArgs& r, double* slots, double* red) {
   double g = 0.0;
-  for (int i = threadIdx.x; i < r.n_gn; i += NTH) g += part[i];
+  for (int i = threadIdx.x; i < r.n_gn; i += NTH) {
+    double x = partial_at(slots + i);
+    for (int n = 0; n < (1 << 20) && __double_as_longlong(x) == NO_PARTIAL; ++n) x = partial_at(slots + i);
+    g += x;
+    __hip_atomic_store(slots + i, __longlong_as_double(NO_PARTIAL), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   g = tile_sum<NTH / 64>(g, red);
-  if (threadIdx.x == 0 && r.gnorm2_out) r.gnorm2_out[0] = g;
+  if (threadIdx.x == 0) r.gnorm2_out[0] = g;
 }
 
 // One workgroup per tile of CB traces, one wavefront per trace (or several
@@ -521,14 +536,12 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
     const double tot = tile_sum<NW>(part, s_red);
     if (tid == 0) {
       if (C::UPD && a.done) {
-        // The partial is in memory before the count says so, and the workgroup that finds every
-        // other one counted reads the partials after that (release and acquire).  The release
-        // writes the XCD's L2 back, which a few workgroups can afford (patch with one virtual
-        // source, 200 of them: 1.0 us a step; 2.5 us for a launch of its own instead).  The
-        // partial itself goes past the L2 at once, 0.3 us less to wait for.
-        __hip_atomic_store(a.part + bid, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
-                 gridDim.x - 2;
+        s_last = false;
+        if (a.red.gnorm2_out) {
+          __hip_atomic_store(a.part + bid, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   gridDim.x - 2;
+        }
       } else {
         a.part[bid] = tot;
       }
@@ -556,7 +569,10 @@ __global__ __launch_bounds__((TraceCfg<NT, MODE>::THREADS)) void k_trace(TraceAr
 // Builds the twiddle table of FftShape for nt (float64 angles, rounded once).
 __global__ void k_twiddles(float2* tw, int nt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 2 * nt - 1) tw[i] = make_float2(0.f, 0.f);  // past the tables: the count of TraceArgs::done
+  // past the tables: the slots of the partials and the count of TraceArgs::done
+  if (i >= 2 * nt - 1 - red_in_update(nt) && i < 2 * nt - 1)
+    reinterpret_cast<long long*>(tw)[i] = NO_PARTIAL;
+  if (i == 2 * nt - 1) tw[i] = make_float2(0.f, 0.f);
   const int n2 = nt / 2;
   const int np8 = n2 >= 512 ? 3 : 2;
   const int rem = n2 / (np8 == 3 ? 512 : 64);

@@ -32,3 +32,20 @@ def test_same_bits_every_time(nr, nvs, nt):
         assert abs(loss[j].item() - lo) <= 2e-6 * lo
         assert abs(gn[j].item() - np.sum(go ** 2)) <= 4e-6 * np.sum(go ** 2)
     assert H(G).any()
+
+
+@pytest.mark.parametrize("nt", [128, 256, 512, 1024])
+@pytest.mark.parametrize("blocks", [1, 64, 128, 129, 254, 256])
+def test_a_norm_that_is_not_finite_leaves_nothing_behind(nt, blocks):
+    """Both sides of the largest number of workgroups, and NaN and infinite norms between."""
+    ns, nf, nb = 6, 20, 3
+    nr = max(blocks // (2 if nt >= 512 else 1), 1)
+    d, u, r = random_case(ns, nr, 16, nt, seed=nr + nt)
+    plan = make_plan(d, u, nb_max=nb, nf=nf)
+    idx = torch.tensor([4, 0, 2], dtype=torch.int32, device="cuda")
+    lo, go = freq.batch_loss_grad(d, r, u, np.array([4, 0, 2]), nf)
+    for bad in (float("nan"), float("inf"), 3e38):
+        assert not torch.isfinite(plan.mdd_stoch_grad(torch.full_like(T(r), bad), idx)[2]).item()
+        _, loss, gn = plan.mdd_stoch_grad(T(r), idx)
+        assert abs(loss.item() - lo) <= 2e-6 * lo
+        assert abs(gn.item() - np.sum(go ** 2)) <= 4e-6 * np.sum(go ** 2)
