@@ -298,15 +298,17 @@ void k_gemm_split(GemmArgs a) {
   float2 sd = make_float2(1.f, 1.f);                // D's scale and its inverse (fp16, not OWN)
   if constexpr (F16 && !OWN) sd = pow2_scale_pair(a.dmax[k]);
 
-  // D_{b,k} for the forward product: wavefront w stages rows 16 w .. 16 w + 15, a lane eight
-  // receivers of one row; rows without a source and receivers past the padded row are out of
+  // D_{b,k} for the forward product: staging wavefront w takes rows 16 w .. 16 w + 15, a lane
+  // eight receivers of one row (the last wavefront is the first to stage: with few column
+  // blocks it has no block of its own); rows without a source and receivers past the padded row are out of
   // bounds: zeros.
   const char* dbase = reinterpret_cast<const char*>(a.Df + (long long)k * a.dns * a.nrp);
   const unsigned dbytes = (unsigned)a.dns * (unsigned)a.nrp * 8u;
   auto chunk_at = [&](int c) {
     return buffer_at(dbase + (long long)c * KC * 8, dbytes - (unsigned)(c * KC) * 8u);
   };
-  const int frow = 16 * wave + (lane >> 2), fg = 8 * (lane & 3);
+  const int sw = NW - 1 - wave;
+  const int frow = 16 * sw + (lane >> 2), fg = 8 * (lane & 3);
   const int fsrc = __shfl(drow, frow, 64);
   const unsigned foff = ((unsigned)fsrc * (unsigned)a.nrp + fg) * 8u;
   auto load_f = [&](float4 (&d)[4], int c) {
@@ -316,7 +318,7 @@ void k_gemm_split(GemmArgs a) {
     for (int q = 0; q < 4; ++q) d[q] = buffer_get4(db, in ? foff + 16u * q : PAST_END);
   };
   auto stage_f = [&](int slot, float4 (&d)[4]) {
-    if (wave < NBT) {
+    if (sw < NBT) {
       float x[8], y[8];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -347,7 +349,7 @@ void k_gemm_split(GemmArgs a) {
   // whose negated imaginary part is Im D.  A half-empty k-step keeps the 16x16x32 shape:
   // with 16x16x16 products at the end of the same sums, two of a tile's four result registers
   // were wrong by 1e-4 in one of the instances (fp16, 48 rows).
-  const int akk = wave >> 1, ar = 16 * (wave & 1) + lr;
+  const int akk = sw >> 1, ar = 16 * (sw & 1) + lr;
   unsigned aoff[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
