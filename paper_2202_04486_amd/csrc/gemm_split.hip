@@ -348,7 +348,10 @@ void k_gemm_split(GemmArgs a) {
   // and 2 w' + 1 (zeros where the second is past the batch); the left operand is conj(D),
   // whose negated imaginary part is Im D.  A half-empty k-step keeps the 16x16x32 shape:
   // with 16x16x16 products at the end of the same sums, two of a tile's four result registers
-  // were wrong by 1e-4 in one of the instances (fp16, 48 rows).
+  // were wrong by 1e-4, and not the same from run to run, in one of the instances (fp16, 48
+  // rows).  That is not explained: staging, barriers and scaling were those of this kernel, and
+  // in the assembly of that form, built again, every read of a product's result comes 8 or more
+  // issue slots after it, which the 4 passes of these products ask for.
   const int akk = sw >> 1, ar = 16 * (sw & 1) + lr;
   unsigned aoff[8];
 #pragma unroll
