@@ -447,30 +447,38 @@ void k_gemm_rows(GemmArgs a, int nslot) {
       step(v, std::integral_constant<int, 1>{}, rbuf[1], rbuf[0]);
       if (++v == nc) break;
     }
-#pragma unroll
-    for (int t = 0; t < NBT; ++t) {               // the last compensation
-      if constexpr (PREC == MDD_PREC_FP32) re[t] -= acc[t].t2;
-      else re[t] += acc[t].t2;
-      im[t] += acc[t].t3;
-    }
     if constexpr (KIND == GK_FUSED && NBT >= 3) load_u();
-    if constexpr (NP > 1) {                       // the parts' sums, added in order
-      __shared__ float2 s_sum[NP][MB][16];
+    if constexpr (NP > 1) {  // the parts' sums with what they lack, in order: one rounding in all
+      __shared__ double2 s_sum[NP][MB][16];
 #pragma unroll
       for (int t = 0; t < NBT; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s_sum[part][t * 16 + lq * 4 + e][lr] = make_float2(re[t][e], im[t][e]);
+        for (int e = 0; e < 4; ++e) {
+          const double er = PREC == MDD_PREC_FP32 ? -acc[t].t2[e] : acc[t].t2[e];
+          s_sum[part][t * 16 + lq * 4 + e][lr] = make_double2(re[t][e] + er, im[t][e] + (double)acc[t].t3[e]);
+        }
       __syncthreads();
 #pragma unroll
       for (int t = 0; t < NBT; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float2 z = s_sum[0][t * 16 + lq * 4 + e][lr];
+          double2 z = s_sum[0][t * 16 + lq * 4 + e][lr];
 #pragma unroll
-          for (int p = 1; p < NP; ++p) z = cadd(z, s_sum[p][t * 16 + lq * 4 + e][lr]);
-          re[t][e] = z.x;
-          im[t][e] = z.y;
+          for (int p = 1; p < NP; ++p) {
+            const double2 y = s_sum[p][t * 16 + lq * 4 + e][lr];
+            z.x += y.x;
+            z.y += y.y;
+          }
+          re[t][e] = (float)z.x;
+          im[t][e] = (float)z.y;
         }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NBT; ++t) {               // the last compensation
+        if constexpr (PREC == MDD_PREC_FP32) re[t] -= acc[t].t2;
+        else re[t] += acc[t].t2;
+        im[t] += acc[t].t3;
+      }
     }
   }
 
