@@ -1056,8 +1056,8 @@ def main():
             "products_speedup_vs_fp32_cgemm": pf.get("gemm_speedup_vs_fp32_cgemm"),
             "target": ">= 2x the plain fp32 form at gradient rel. err <= 1e-3",
             "note": "fp32 is the float32 form the library ships (three real products per complex "
-                    "multiply-add in the tiled and warp-specialised kernels); fp32_cgemm (four) is "
-                    "a secondary comparison.  The update kernel (inverse transform, mask, Adam, "
+                    "multiply-add, four in the fused product of at most 16 rows and 224 "
+                    "receivers); fp32_cgemm (four everywhere) is a secondary comparison.  The update kernel (inverse transform, mask, Adam, "
                     "next model's transform) is the same in every form and HBM-bound, so the "
                     "whole-step ratio stays far below the products' ratio under Adam"}
     if not args.no_cpu_baseline:

@@ -33,7 +33,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 // past the end and drops stores there.  That takes the address arithmetic, the clamping
 // and the zeroing of partial chunks out of the vector unit.
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 constexpr unsigned PAST_END = 0xffffffffu;        // an offset that is out of bounds for every buffer
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
