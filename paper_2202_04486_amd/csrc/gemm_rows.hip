@@ -106,9 +106,11 @@ __device__ __forceinline__ void fold(Tile& t, floatx4& re, floatx4& im) {
     if constexpr (PREC == MDD_PREC_FP32) {
       t.t2[i] = -er;                              // subtracted
       t.t3[i] = ei;
-    } else {                                      // an infinite sum has no error (inf - inf)
-      t.t2[i] = er == er ? er : 0.f;
-      t.t3[i] = ei == ei ? ei : 0.f;
+    } else {
+      // Beside an infinite sum the error is inf - inf: the median of a NaN and two bounds is the
+      // lower one, which changes no infinity.  A finite sum's error is below 2^104.
+      t.t2[i] = __builtin_amdgcn_fmed3f(er, -0x1p104f, 0x1p104f);
+      t.t3[i] = __builtin_amdgcn_fmed3f(ei, -0x1p104f, 0x1p104f);
     }
     re[i] = sr;
     im[i] = si;
