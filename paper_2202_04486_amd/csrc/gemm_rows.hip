@@ -102,15 +102,14 @@ __device__ __forceinline__ void fold(Tile& t, floatx4& re, floatx4& im) {
     const float xr = PREC == MDD_PREC_FP32 ? t.t1[i] - t.t2[i] : t.t2[i];
     const float xi = PREC == MDD_PREC_FP32 ? t.t1[i] + t.t3[i] : t.t3[i];
     const float sr = re[i] + xr, si = im[i] + xi;
-    const float er = xr - (sr - re[i]), ei = xi - (si - im[i]);
     if constexpr (PREC == MDD_PREC_FP32) {
-      t.t2[i] = -er;                              // subtracted
-      t.t3[i] = ei;
+      t.t2[i] = (sr - re[i]) - xr;                // subtracted
+      t.t3[i] = xi - (si - im[i]);
     } else {
       // Beside an infinite sum the error is inf - inf: the median of a NaN and two bounds is the
       // lower one, which changes no infinity.  A finite sum's error is below 2^104.
-      t.t2[i] = __builtin_amdgcn_fmed3f(er, -0x1p104f, 0x1p104f);
-      t.t3[i] = __builtin_amdgcn_fmed3f(ei, -0x1p104f, 0x1p104f);
+      t.t2[i] = __builtin_amdgcn_fmed3f(xr - (sr - re[i]), -0x1p104f, 0x1p104f);
+      t.t3[i] = __builtin_amdgcn_fmed3f(xi - (si - im[i]), -0x1p104f, 0x1p104f);
     }
     re[i] = sr;
     im[i] = si;
