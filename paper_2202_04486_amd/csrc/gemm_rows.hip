@@ -571,10 +571,11 @@ void k_gemm_rows(GemmArgs a, int nslot) {
 template <int PREC, int NBT, bool RES, int NW, int NP = 1>
 hipError_t launch_nw(int kind, const GemmArgs& a, int nslot, hipStream_t s) {
   const size_t sm = (size_t)RowsCfg<NBT>::ESZ * RowsCfg<NBT>::SLOT * nslot * NP;
+  constexpr size_t sums = NP > 1 ? sizeof(double2) * NP * RowsCfg<NBT>::MB * 16 : 0;  // the kernel's own LDS
   const int ncg = (a.nvb + NW - 1) / NW;
   const dim3 grid(a.nf * ncg), block(64 * NW * NP);
   auto go = [&](auto kernel) {
-    if (sm > 65536)
+    if (sm + sums > 65536)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     hipLaunchKernelGGL(kernel, grid, block, sm, s, a, nslot);
